@@ -639,6 +639,13 @@ __device__ __forceinline__ lanev<U, C> new_state(const RoundArgs &a, const lanev
     return xn;
 }
 
+// How many of the previous messages into a worker of `deg` neighbours its
+// own messages pass on: all of them, or none at a leaf, whose one message
+// m_{i->j} excludes j's.  The leaves' in-messages are therefore not read: 2
+// of the 140 rows of a 16-worker chain with momentum, 8 of those of a
+// balanced or a pair of double binary trees, 4-8% of a random or hub tree's.
+__device__ __forceinline__ int relayed(int deg) { return deg > 1 ? deg : 0; }
+
 // Messages out of worker i (Alg. 1, 3, 4): for each neighbour j (slot
 // s0+q), m_{i->j} = p_i + sum over the other in-edges b != q, ascending, of
 // the previous round's m_{k->i}; a lost message is written as zeros.  `o`
@@ -776,7 +783,7 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
             if (deg <= kMaxDegInRegs) {
 #pragma unroll
                 for (int b = 0; b < kMaxDegInRegs; ++b) {
-                    if (b < deg) {
+                    if (b < relayed(deg)) {
                         const int in_slot = uniform(a.rev[s0 + b]);
                         o[b] = load_lane<1, 1, NT, false>(a.ring_prev + ring_off(a, in_slot, sbase),
                                                           lane, oks);
@@ -814,7 +821,7 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
         if (deg <= kMaxDegInRegs) {
 #pragma unroll
             for (int b = 0; b < kMaxDegInRegs; ++b) {
-                if (b < deg) {
+                if (b < relayed(deg)) {
                     const int in_slot = uniform(a.rev[s0 + b]);
                     o[b] = load_lane<U, C, NT, TAIL>(a.ring_prev + ring_off(a, in_slot, base), lane, ok);
                 }
@@ -1007,7 +1014,7 @@ __global__ void __launch_bounds__(1024) relaysum_cluster_kernel(RoundArgs a, Clu
         lanev<U, C> o[MD];
 #pragma unroll
         for (int b = 0; b < MD; ++b) {
-            if (b < deg) {
+            if (b < relayed(deg)) {
                 const int in_pos = ldc(k.rpos + ldc(a.rev + s0 + b));
                 o[b] = load_lane<U, C, NT, TAIL>(a.ring_prev + ring_off(a, in_pos, base), lane, ok);
             }
@@ -1247,13 +1254,13 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
         if (dega <= kMaxDegInRegs) {
 #pragma unroll
             for (int q = 0; q < kMaxDegInRegs; ++q)
-                if (q < dega)
+                if (q < relayed(dega))
                     oa[q] = load_pairs(a.ring_prev + ring_off(a, ldc(a.rev + s0a + q), tbase), lane, ok_r);
         }
         if (degb <= kMaxDegInRegs) {
 #pragma unroll
             for (int q = 0; q < kMaxDegInRegs; ++q)
-                if (q < degb)
+                if (q < relayed(degb))
                     ob[q] = load_pairs(b.ring_prev + ring_off(b, ldc(b.rev + s0b + q), tbase), lane, ok_r);
         }
         const lanev<U, 4> pay = payload<R, U, 4>(a, xv, gv, s1, s2);
@@ -1371,7 +1378,7 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_seq_kernel(RoundArgs a, R
         if (dega <= kMaxDegInRegs) {
 #pragma unroll
             for (int q = 0; q < kMaxDegInRegs; ++q)
-                if (q < dega)
+                if (q < relayed(dega))
                     oa[q] = load_pairs(a.ring_prev + ring_off(a, ldc(a.rev + s0a + q), tbase), lane, ok_r);
         }
         const lanev<U, 4> pay = payload<R, U, 4>(a, xv, gv, s1, s2);
@@ -1423,7 +1430,7 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_seq_kernel(RoundArgs a, R
             if (degb <= MB) {
 #pragma unroll
                 for (int q = 0; q < MB; ++q)
-                    if (q < degb)
+                    if (q < relayed(degb))
                         ob[p][q] = load_pairs(b.ring_prev + ring_off(b, ldc(b.rev + s0b + q), tbase), lane, ok_r);
             }
         }
@@ -1570,14 +1577,14 @@ __global__ void __launch_bounds__(1024) relaysum_cluster_dtree_kernel(RoundArgs 
         if (dega <= MD) {
 #pragma unroll
             for (int q = 0; q < MD; ++q)
-                if (q < dega)
+                if (q < relayed(dega))
                     oa[q] = load_pairs(a.ring_prev + ring_off(a, ldc(ka.rpos + ldc(a.rev + s0a + q)), tbase),
                                        lane, ok_r);
         }
         if (degb <= MD) {
 #pragma unroll
             for (int q = 0; q < MD; ++q)
-                if (q < degb)
+                if (q < relayed(degb))
                     ob[q] = load_pairs(b.ring_prev + ring_off(b, ldc(kb.rpos + ldc(b.rev + s0b + q)), tbase),
                                        lane, ok_r);
         }
@@ -1832,7 +1839,7 @@ __global__ void __launch_bounds__(256) relaysum_pass_a(RoundArgs a) {
             lanev<1, C> o[MD];
 #pragma unroll
             for (int b = 0; b < MD; ++b)
-                if (b < deg)
+                if (b < relayed(deg))
                     o[b] = load_lane<1, C>(a.ring_prev + ring_off(a, a.rev[s0 + b], off), 0, ok);
             const lanev<1, C> p = payload<R, 1, C>(a, xv, gv, s1, s2);
             if constexpr (T::nesterov || T::adam) store_lane<1, C>(a.s1 + row, 0, ok, s1);
