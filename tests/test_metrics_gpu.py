@@ -79,3 +79,33 @@ def test_rounds_with_lr_zero_pull_models_together():
                 assert abs(dist - want) <= 1e-12 * want
                 seen.append(dist)
     assert seen[0] < consensus_distance(x0)[0] and seen[1] < seen[0] and seen[2] < seen[1], seen
+
+
+@pytest.mark.parametrize("n,d,offset", [(2, 255, 0), (8, 256, 0), (9, 257, 1), (32, 1_022, 3),
+                                        (33, 1_024, 0), (64, 1_025, 1), (65, 2_049, 2), (128, 511, 0),
+                                        (129, 4_096, 0), (1_003, 1_030, 1), (40, 530_002, 1)])
+def test_worker_groups_and_tile_edges(n, d, offset):
+    """Where the work splits: one, two, four and eight waves to a tile of 256
+    coordinates (up to 32, 64, 128 and more workers), whole and partial
+    batches of 8 workers, whole tiles, partial last ones and partial last
+    16-byte chunks, and more tiles than blocks with waves sharing a tile.
+    Models far from zero with small deviations: 100 plus N(0, 1e-3), whose
+    squares' difference would cancel.  Bound: each deviation carries a few
+    2^-53 of the mean over deviations of 1e-3, about 1e5 times smaller than
+    the mean, so 1e-10 relative holds with room."""
+    announce(f"consensus distance n={n} d={d} offset={offset}")
+    rng = np.random.default_rng(n * 7 + d)
+    x = (100.0 + 1e-3 * rng.standard_normal((n, d))).astype(np.float32)
+    buf = torch.zeros(n * d + offset, dtype=torch.float32, device="cuda")
+    xd = buf[offset:].view(n, d)
+    xd.copy_(torch.from_numpy(x))
+    with rs.RelaySum(n, d, wl.chain_edges(n)) as h:
+        dist, spread = h.consensus_distance(xd)
+        assert h.consensus_distance(xd) == (dist, spread)
+        want, want_spread = consensus_distance(x)
+        assert abs(dist - want) <= 1e-10 * want, (dist, want)
+        assert abs(spread - want_spread) <= 1e-10 * want_spread, (spread, want_spread)
+        # One NaN makes the distance NaN and leaves the other coordinates' spread.
+        xd[n // 2, d - 1] = float("nan")
+        dist, spread = h.consensus_distance(xd)
+        assert np.isnan(dist) and abs(spread - consensus_distance(x[:, :-1])[1]) <= 1e-10 * want_spread
