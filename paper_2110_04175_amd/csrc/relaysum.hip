@@ -407,6 +407,7 @@ struct RoundArgs {
     float bc2_sqrt;           // Adam: sqrt(1 - beta2^t), rounded once from double
     int64_t spill_base;       // tile kernel with a spill: first coordinate past the grid's tiles
     int32_t spill;            //   and the spill coordinates of each workgroup (at most 64)
+    int32_t run_shift;        // log2 of the neighbouring tiles on one XCD (xcd_run_place)
     int32_t nhubs;            // workers of more than kMaxDegInRegs2 neighbours (hubs), by degree
     const int32_t *hubs;      //   class: the hub kernels take them, pass A and the clusters do not
     // Hub kernels ahead of the cluster kernel: ring positions of the slots
@@ -685,26 +686,38 @@ __device__ __forceinline__ void emit_messages(const RoundArgs &a, float *s_msg, 
     }
 }
 
-// Tile of this workgroup.  Workgroups go to the eight XCDs round robin
-// (workgroup b to XCD b mod 8), each XCD with its own L2.  Two consecutive
-// tiles share a 128-byte line on every row whose start is not line-aligned
-// (row i starts i*d*4 bytes into its array; on the 16-worker chain at
-// d = 9.75M every odd row starts 64 bytes into a line), and on two XCDs that
-// line is fetched from memory twice: 1.9% more reads than the round needs.
-// Pairing tiles 2k and 2k+1 on one XCD (workgroups b and b+8 of each group
-// of 16, dispatched close together) fetches it once.  On MI355X the
-// single-tree tile kernel took 0.5-2% less time per round on that chain
-// (FETCH_SIZE 3.101 -> 3.074 GB; eq. robust and Alg. 4 1-2% less, Alg. 3
-// the same); groups of 4 or 8 tiles per XCD measured no gain.  The
-// cache-allocating short rounds (3% slower paired), Adam (2-3% slower) and
-// the double-tree kernels (1-4% slower, with their packed ring layout) keep
-// the plain order.
-template <bool PAIRED>
-__device__ __forceinline__ int64_t tile_of_workgroup() {
-    const int64_t b = blockIdx.x;
-    if constexpr (!PAIRED) return b;
-    const int64_t full = (int64_t)gridDim.x & ~(int64_t)15;
-    return b < full ? 16 * (b >> 4) + 2 * (b & 7) + ((b >> 3) & 1) : b;
+// Place of this workgroup, b, in the order of the tiles (run_shift_of says
+// which launches group how many).  Workgroups go to the eight
+// XCDs round robin (workgroup b to XCD b mod 8), each with its own L2; with
+// `shift` the places 2^shift * k .. 2^shift * (k + 1) - 1 go to one XCD
+// (workgroups b, b + 8, .. of each group of 8 * 2^shift, dispatched close
+// together).
+__device__ __forceinline__ unsigned xcd_run_place(int shift) {
+    const unsigned b = blockIdx.x;
+    const unsigned full = (gridDim.x >> (3 + shift)) << (3 + shift);
+    const unsigned in = b & ((8u << shift) - 1);
+    return b < full ? (b - in) + ((in & 7) << shift) + (in >> 3) : b;
+}
+
+// Cluster and tile of this workgroup: the K clusters of a tile on
+// neighbouring workgroups, and with a.run_shift the 2^run_shift neighbouring
+// tiles of a cluster on one XCD.
+__device__ __forceinline__ void cluster_of_workgroup(const RoundArgs &a, int count, int *cl,
+                                                     int64_t *tile) {
+    const unsigned K = (unsigned)count;
+    const unsigned p = xcd_run_place(a.run_shift);
+    const unsigned groups = (unsigned)(a.ntiles >> a.run_shift);
+    const unsigned per = K << a.run_shift;
+    const unsigned g = p / per;
+    if (g < groups) {
+        const unsigned r = p - g * per;
+        *cl = (int)(r >> a.run_shift);
+        *tile = ((int64_t)g << a.run_shift) + (r & ((1u << a.run_shift) - 1));
+    } else {
+        const unsigned r = p - groups * per;   // the last tiles, fewer than a run
+        *cl = (int)(r % K);
+        *tile = ((int64_t)groups << a.run_shift) + r / K;
+    }
 }
 
 // ---- tile kernel -------------------------------------------------------------
@@ -740,7 +753,7 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int64_t tile = tile_of_workgroup<NT && !T::adam>();
+    const int64_t tile = xcd_run_place(a.run_shift);
     const int64_t base = tile * kSlot;   // float offset of the tile in every row
     // Valid floats of each of this lane's chunks: C, 0 past the row end, and
     // with TAIL (d % C != 0) fewer in the chunk that holds the row's last
@@ -985,8 +998,9 @@ __global__ void __launch_bounds__(1024) relaysum_cluster_kernel(RoundArgs a, Clu
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int cl = (int)(blockIdx.x % (unsigned)k.count);
-    const int64_t tile = blockIdx.x / (unsigned)k.count;
+    int cl;
+    int64_t tile;
+    cluster_of_workgroup(a, k.count, &cl, &tile);
     const int64_t base = tile * kSlot;
     const int32_t *mem = k.members + (int64_t)cl * k.cap;
     int ok[U];
@@ -1225,7 +1239,7 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int64_t tile = blockIdx.x;
+    const int64_t tile = xcd_run_place(a.run_shift);
     const int64_t base = tile * (64 * U * 4);   // model coordinate of the tile
     const int64_t tbase = tile * kSlot;         // carried coordinate in each tree
     int ok[U];   // valid model coordinates in each of the lane's chunks
@@ -1349,7 +1363,7 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_seq_kernel(RoundArgs a, R
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int64_t tile = blockIdx.x;
+    const int64_t tile = xcd_run_place(a.run_shift);
     const int64_t base = tile * (64 * U * 4);   // model coordinate of the tile
     const int64_t tbase = tile * kSlot;         // carried coordinate in each tree
     int ok[U];   // valid model coordinates in each of the lane's chunks
@@ -1539,8 +1553,9 @@ __global__ void __launch_bounds__(1024) relaysum_cluster_dtree_kernel(RoundArgs 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int cl = (int)(blockIdx.x % (unsigned)ka.count);
-    const int64_t tile = blockIdx.x / (unsigned)ka.count;
+    int cl;
+    int64_t tile;
+    cluster_of_workgroup(a, ka.count, &cl, &tile);
     const int64_t base = tile * (64 * U * 4);
     const int64_t tbase = tile * kSlot;
     int ok[U];
@@ -2480,6 +2495,7 @@ struct relaysum_s {
         kernelc_fn fc1 = nullptr, fc2 = nullptr;
         kerneld_fn fd1 = nullptr, fd2 = nullptr;
         size_t lds = 0;
+        int32_t run_shift = 0;   // log2 of the neighbouring tiles on one XCD
         int32_t spill = 0;       // tile kernel with a spill sub-tile: its coordinates
         int64_t spill_grid = 0;  //   per workgroup, and the workgroups
     } launch[2][kNumRules];      // [128-bit][rule], filled on first use
@@ -2842,6 +2858,45 @@ static bool locate_slot(const relaysum_t *h, int32_t slot, int *tree, int32_t *l
 // aligned rows.
 enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kPathClusterDTree };
 
+// log2 of the neighbouring tiles that one XCD takes (xcd_run_place) on a path
+// with rows of d floats; `streams`: a round past the caches.
+//
+// Two neighbouring tiles share a line of every row that does not start on
+// one (row i starts i*d*4 bytes into its array).  On two XCDs that line is
+// read from memory twice and written as two partial lines; on one XCD, by
+// workgroups dispatched close together, its L2 joins them.  Memory takes
+// partial 64-byte blocks dearest, so rows with d % 16 != 0 gain most from
+// long runs, and rows of whole 128-byte lines (d % 32 == 0) nothing.  ms per
+// round on MI355X, same box, runs of 1 | 2 | 8 | 16 tiles:
+//   tile kernel   chain of 16, d = 9.75M        .922 | .915 | .917 | .923
+//                 the same, d = 9,750,001       .993 | .976 | .971 | .975
+//                 the same, Adam               1.265 | 1.307 | 1.243 | 1.247
+//                 Adam, d = 9.75M              1.180 | 1.215 | 1.199 | 1.200
+//   cluster       chain of 64, d = 9.75M       4.134 | 4.176 | 4.128 | 4.087
+//                 2,000 with hubs, d = 150,000 2.203 | 2.178 | 2.117 | 2.103
+//                 random 1,000, d = 200,001    1.571 | 1.537 | 1.487 | 1.479
+//                 random 256, d = 1M           1.711 | 1.728 | 1.702 | 1.717
+//   double trees, one after the other
+//                 64, d = 9.75M                4.092 | 4.388 | 4.038 | 3.982
+//                 40, d = 4M                    .976 | 1.000 | 1.002 | .984
+// Pairs on the first row cut FETCH_SIZE from 3.101 to 3.074 GB.  Runs of 32
+// and 64 tiles were no faster.  Rounds that stay in the caches find the line
+// there (equal to 1%), and the double-tree kernel with both trees in LDS was
+// slower with every run (16 workers, d = 9.75M: .889 | .925 | .898 | .899).
+static int run_shift_of(Path path, bool adam, int64_t d, bool streams) {
+    switch (path) {
+        case kPathTile:
+            if (!streams) return 0;
+            return d % 16 != 0 ? 3 : adam ? 0 : 1;
+        case kPathDTreeSeq:
+        case kPathCluster:
+        case kPathClusterDTree:
+            return d % 32 != 0 ? 4 : 0;
+        default:
+            return 0;
+    }
+}
+
 static Path path_of(const relaysum_t *h) {
     if (h->tile && h->ntrees == 1) return kPathTile;
     if (h->tile) return kPathDTree;
@@ -2891,6 +2946,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
                 (rows * (size_t)h->n * (size_t)h->d + 2 * ring_parity_floats(h)) * sizeof(float);
             const bool nt = working_set > kMallBytes / 2;
             L.fn = pick_tile(rule, h->pw, nt, h->d % 4 != 0);
+            L.run_shift = run_shift_of(kPathTile, adam, h->d, nt);
             fn = (const void *)L.fn;
             const int floats_per_lane = 4 * kU4;
             lds = std::max(tile_lds_bytes(h->n, h->tr[0].e2, floats_per_lane, mean), cap_lds);
@@ -2944,6 +3000,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             break;
         case kPathDTreeSeq:
             L.fn2 = pick_dtree_seq(rule, h->pw, h->d % 4 != 0);
+            L.run_shift = run_shift_of(kPathDTreeSeq, adam, h->d, true);
             fn = (const void *)L.fn2;
             lds = std::max(dtree_seq_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
@@ -2955,6 +3012,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
                               h->d % 4 != 0,
                               h->d % 4 == 0, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
+            L.run_shift = run_shift_of(kPathCluster, adam, h->d, true);
             fn = (const void *)L.fc1;
             lds = cluster_lds_bytes(h->n, h->tr[0].e2, h->cl_slots[0], mean, h->cl_relay);
             if (h->cl_relay) lds = std::max(lds, cap_lds);
@@ -2963,6 +3021,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
         case kPathClusterDTree:
             if (!pick_cluster_dtree(rule, h->d % 4 != 0, h->cl_cap / kMaxWaves, &L.fd1, &L.fd2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
+            L.run_shift = run_shift_of(kPathClusterDTree, adam, h->d, true);
             fn = (const void *)L.fd1;
             // Both trees' message tiles of the largest cluster; no residency cap.
             lds = ((size_t)h->cl_slots[0] + h->cl_slots[1]) * kWave * kDTreeU * 2 * sizeof(float);
@@ -3269,6 +3328,8 @@ int relaysum_step_ex(relaysum_t *h, float *x, const float *g, float *state1, flo
         const int rc = resolve_launch(h, rule, c4);
         if (rc != RELAYSUM_OK) return rc;
     }
+
+    for (RoundArgs &a : ta) a.run_shift = L.run_shift;
 
     if (path == kPathTile) {
         RoundArgs &a = ta[0];
@@ -4059,6 +4120,7 @@ extern "C" int relaysum_step_static(int32_t n, int64_t d, const int32_t *edges, 
     a.d = d;
     a.nchunks = d / 4;
     a.ntiles = ntiles;
+    a.run_shift = run_shift_of(kPathTile, false, d, nt);
     a.cnt_prev = cnt + (size_t)prev * e2;
     a.cnt_next = cnt + (size_t)next * e2;
     a.nbar_out = cnt + 2 * (size_t)e2;
