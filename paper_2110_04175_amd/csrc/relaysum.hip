@@ -1138,17 +1138,19 @@ typedef lanev<kDTreeU, 2> pair2_t;
 static_assert(kDTreeU == 2 && kRingShift >= 9,
               "packed_pos assumes 64 lanes x 2 chunks x 2 floats per 256-coordinate block");
 
+template <bool NT = true>
 __device__ __forceinline__ pair2_t load_pairs(const float *tile, int lane, bool ok) {
     pair2_t r;
     float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (ok) load_chunk<4>(tile + lane * 4, t);
+    if (ok) load_chunk<4, NT>(tile + lane * 4, t);
     r.v[0][0] = t[0]; r.v[0][1] = t[1]; r.v[1][0] = t[2]; r.v[1][1] = t[3];
     return r;
 }
 
+template <bool NT = true>
 __device__ __forceinline__ void store_pairs(float *tile, int lane, bool ok, const pair2_t &a) {
     const float t[4] = {a.v[0][0], a.v[0][1], a.v[1][0], a.v[1][1]};
-    if (ok) store_chunk<4>(tile + lane * 4, t);
+    if (ok) store_chunk<4, NT>(tile + lane * 4, t);
 }
 
 __device__ __forceinline__ void lds_put_pairs(float *slot, int lane, const pair2_t &a) {
@@ -1163,7 +1165,7 @@ __device__ __forceinline__ pair2_t lds_get_pairs(const float *slot, int lane) {
 }
 
 // emit_messages for one tree of the double-tree kernel (packed tiles).
-template <int MD>
+template <int MD, bool NT = true>
 __device__ __forceinline__ void emit_pair_messages(const RoundArgs &a, float *s_msg, int lane,
                                                    bool ok, int64_t tbase, int s0, int deg,
                                                    const pair2_t &p, const pair2_t (&o)[MD]) {
@@ -1177,7 +1179,7 @@ __device__ __forceinline__ void emit_pair_messages(const RoundArgs &a, float *s_
                 for (int b = 0; b < MD; ++b)
                     if (b < deg && b != q) m = add_lane<kDTreeU, 2>(m, o[b]);
                 if (lost(a, s0 + q)) m = zero_lane<kDTreeU, 2>();
-                store_pairs(a.ring_next + ring_off(a, s0 + q, tbase), lane, ok, m);
+                store_pairs<NT>(a.ring_next + ring_off(a, s0 + q, tbase), lane, ok, m);
                 lds_put_pairs(s_msg + (s0 + q) * kSlot, lane, m);
             }
         }
@@ -1188,10 +1190,10 @@ __device__ __forceinline__ void emit_pair_messages(const RoundArgs &a, float *s_
                 if (b == q) continue;
                 const int in_slot = ldc(a.rev + s0 + b);
                 m = add_lane<kDTreeU, 2>(
-                    m, load_pairs(a.ring_prev + ring_off(a, in_slot, tbase), lane, ok));
+                    m, load_pairs<NT>(a.ring_prev + ring_off(a, in_slot, tbase), lane, ok));
             }
             if (lost(a, s0 + q)) m = zero_lane<kDTreeU, 2>();
-            store_pairs(a.ring_next + ring_off(a, s0 + q, tbase), lane, ok, m);
+            store_pairs<NT>(a.ring_next + ring_off(a, s0 + q, tbase), lane, ok, m);
             lds_put_pairs(s_msg + (s0 + q) * kSlot, lane, m);
         }
     }
@@ -1213,7 +1215,12 @@ __device__ __forceinline__ void emit_pair_messages(const RoundArgs &a, float *s_
 // 64 chunks further on): pairs past the tree's length carry values of
 // missing coordinates, which no row ever receives; the ring holds whole ring
 // tiles, so the 16-byte access stays in bounds on the ragged last tile.
-template <int PW, int R, bool TAIL>
+//
+// A short round whose rows and ring stay in the MALL runs with
+// cache-allocating accesses (NT = false, as in the tile kernel): on MI355X 24
+// workers at d = 150,001 30.6 -> 26.7 us per round, 16 with Adam at d = 250,000
+// 34.5 -> 30.6 us, 16 at d = 270,000 (of the range's end) 31.6 -> 31.3 us.
+template <int PW, int R, bool NT, bool TAIL>
 __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, RoundArgs b) {
     using T = RuleOf<R>;
     constexpr int U = kDTreeU;
@@ -1258,10 +1265,10 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
         if (i >= a.n) break;
         const int64_t row = (int64_t)i * a.d + base;
         lanev<U, 4> xv = zero_lane<U, 4>(), s1 = zero_lane<U, 4>(), s2 = zero_lane<U, 4>();
-        if constexpr (T::reads_x) xv = load_lane<U, 4, true, TAIL>(a.x + row, lane, ok);
-        const lanev<U, 4> gv = load_lane<U, 4, true, TAIL>(a.g + row, lane, ok);
-        if constexpr (T::uses_s1) s1 = load_lane<U, 4, true, TAIL>(a.s1 + row, lane, ok);
-        if constexpr (T::uses_s2) s2 = load_lane<U, 4, true, TAIL>(a.s2 + row, lane, ok);
+        if constexpr (T::reads_x) xv = load_lane<U, 4, NT, TAIL>(a.x + row, lane, ok);
+        const lanev<U, 4> gv = load_lane<U, 4, NT, TAIL>(a.g + row, lane, ok);
+        if constexpr (T::uses_s1) s1 = load_lane<U, 4, NT, TAIL>(a.s1 + row, lane, ok);
+        if constexpr (T::uses_s2) s2 = load_lane<U, 4, NT, TAIL>(a.s2 + row, lane, ok);
         const int s0a = ldc(a.row_ptr + i), dega = ldc(a.row_ptr + i + 1) - s0a;
         const int s0b = ldc(b.row_ptr + i), degb = ldc(b.row_ptr + i + 1) - s0b;
         pair2_t oa[kMaxDegInRegs], ob[kMaxDegInRegs];
@@ -1269,13 +1276,13 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
 #pragma unroll
             for (int q = 0; q < kMaxDegInRegs; ++q)
                 if (q < relayed(dega))
-                    oa[q] = load_pairs(a.ring_prev + ring_off(a, ldc(a.rev + s0a + q), tbase), lane, ok_r);
+                    oa[q] = load_pairs<NT>(a.ring_prev + ring_off(a, ldc(a.rev + s0a + q), tbase), lane, ok_r);
         }
         if (degb <= kMaxDegInRegs) {
 #pragma unroll
             for (int q = 0; q < kMaxDegInRegs; ++q)
                 if (q < relayed(degb))
-                    ob[q] = load_pairs(b.ring_prev + ring_off(b, ldc(b.rev + s0b + q), tbase), lane, ok_r);
+                    ob[q] = load_pairs<NT>(b.ring_prev + ring_off(b, ldc(b.rev + s0b + q), tbase), lane, ok_r);
         }
         const lanev<U, 4> pay = payload<R, U, 4>(a, xv, gv, s1, s2);
 #pragma unroll
@@ -1285,10 +1292,10 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
         }
         if constexpr (T::keeps_x) old[p] = xv;
         if constexpr (T::mean) old[p] = s1;
-        if constexpr (T::nesterov || T::adam) store_lane<U, 4, true, TAIL>(a.s1 + row, lane, ok, s1);
-        if constexpr (T::adam) store_lane<U, 4, true, TAIL>(a.s2 + row, lane, ok, s2);
-        emit_pair_messages<kMaxDegInRegs>(a, s_msg_a, lane, ok_r, tbase, s0a, dega, pa[p], oa);
-        emit_pair_messages<kMaxDegInRegs>(b, s_msg_b, lane, ok_r, tbase, s0b, degb, pb[p], ob);
+        if constexpr (T::nesterov || T::adam) store_lane<U, 4, NT, TAIL>(a.s1 + row, lane, ok, s1);
+        if constexpr (T::adam) store_lane<U, 4, NT, TAIL>(a.s2 + row, lane, ok, s2);
+        emit_pair_messages<kMaxDegInRegs, NT>(a, s_msg_a, lane, ok_r, tbase, s0a, dega, pa[p], oa);
+        emit_pair_messages<kMaxDegInRegs, NT>(b, s_msg_b, lane, ok_r, tbase, s0b, degb, pb[p], ob);
     }
     __syncthreads();
 #pragma unroll
@@ -1321,8 +1328,8 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
             yn.v[u][0] = ob.v[u][0]; yn.v[u][1] = oa.v[u][0];
             yn.v[u][2] = ob.v[u][1]; yn.v[u][3] = oa.v[u][1];
         }
-        if constexpr (T::mean) store_lane<U, 4, true, TAIL>(a.s1 + row, lane, ok, yn);
-        store_lane<U, 4, true, TAIL>(a.x + row, lane, ok, xn);
+        if constexpr (T::mean) store_lane<U, 4, NT, TAIL>(a.s1 + row, lane, ok, yn);
+        store_lane<U, 4, NT, TAIL>(a.x + row, lane, ok, xn);
     }
 }
 
@@ -2297,23 +2304,28 @@ bool pick_passes(int rule, kernel_fn *pa, kernel_fn *pb, kernel_fn *ph) {
 }
 
 
-template <int R>
+template <int R, bool NT>
 kernel2_fn dtree_for(int pw, bool tail) {
-    if (tail) return pw == 1 ? relaysum_dtree_kernel<1, R, true> : relaysum_dtree_kernel<2, R, true>;
-    return pw == 1 ? relaysum_dtree_kernel<1, R, false> : relaysum_dtree_kernel<2, R, false>;
+    if (tail) return pw == 1 ? relaysum_dtree_kernel<1, R, NT, true> : relaysum_dtree_kernel<2, R, NT, true>;
+    return pw == 1 ? relaysum_dtree_kernel<1, R, NT, false> : relaysum_dtree_kernel<2, R, NT, false>;
 }
 
-kernel2_fn pick_dtree(int rule, int pw, bool tail) {
+template <int R>
+kernel2_fn dtree_for(int pw, bool nt, bool tail) {
+    return nt ? dtree_for<R, true>(pw, tail) : dtree_for<R, false>(pw, tail);
+}
+
+kernel2_fn pick_dtree(int rule, int pw, bool nt, bool tail) {
     if (pw != 1 && pw != 2) return nullptr;
     switch (rule) {
-        case kModelSgd: return dtree_for<kModelSgd>(pw, tail);
-        case kModelNesterov: return dtree_for<kModelNesterov>(pw, tail);
-        case kModelAdam: return dtree_for<kModelAdam>(pw, tail);
-        case kRobustSgd: return dtree_for<kRobustSgd>(pw, tail);
-        case kRobustNesterov: return dtree_for<kRobustNesterov>(pw, tail);
-        case kRobustAdam: return dtree_for<kRobustAdam>(pw, tail);
-        case kGrad: return dtree_for<kGrad>(pw, tail);
-        case kMean: return dtree_for<kMean>(pw, tail);
+        case kModelSgd: return dtree_for<kModelSgd>(pw, nt, tail);
+        case kModelNesterov: return dtree_for<kModelNesterov>(pw, nt, tail);
+        case kModelAdam: return dtree_for<kModelAdam>(pw, nt, tail);
+        case kRobustSgd: return dtree_for<kRobustSgd>(pw, nt, tail);
+        case kRobustNesterov: return dtree_for<kRobustNesterov>(pw, nt, tail);
+        case kRobustAdam: return dtree_for<kRobustAdam>(pw, nt, tail);
+        case kGrad: return dtree_for<kGrad>(pw, nt, tail);
+        case kMean: return dtree_for<kMean>(pw, nt, tail);
         default: return nullptr;
     }
 }
@@ -2930,21 +2942,21 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
     const size_t cap_lds = grid_tiles >= 8 * (int64_t)h->cu_count
                                ? std::min(h->lds_cu / (size_t)(per_cu + 1) + 256, h->lds_limit)
                                : 0;
+    // Cache-allocating accesses when the round's working set (the rows it
+    // reads or writes and both ring parities) takes at most half of the 256
+    // MB MALL, so that the next round finds it there: on the 16-worker heap
+    // at d = 270,000 (117 MB) a round took 27.5-29.0 us instead of 30.6-31.4
+    // us.  Larger rounds stream past the caches (on the 16-worker chain at
+    // d = 9.75M cache-allocating accesses took 1.09 ms per round instead of
+    // 0.93 ms).
+    const size_t rows = 2 + (uses_s1 ? 1 : 0) + (adam ? 1 : 0);
+    const size_t working_set =
+        (rows * (size_t)h->n * (size_t)h->d + 2 * ring_parity_floats(h)) * sizeof(float);
+    const bool nt = working_set > kMallBytes / 2;
     const void *fn = nullptr;
     size_t lds = 0;
     switch (path_of(h)) {
         case kPathTile: {
-            // Cache-allocating accesses when the round's working set (the
-            // rows it reads or writes and both ring parities) takes at most
-            // half of the 256 MB MALL, so that the next round finds it there:
-            // on the 16-worker heap at d = 270,000 (117 MB) a round took
-            // 27.5-29.0 us instead of 30.6-31.4 us.  Larger rounds stream past
-            // the caches (on the 16-worker chain at d = 9.75M cache-allocating
-            // accesses took 1.09 ms per round instead of 0.93 ms).
-            const size_t rows = 2 + (uses_s1 ? 1 : 0) + (adam ? 1 : 0);
-            const size_t working_set =
-                (rows * (size_t)h->n * (size_t)h->d + 2 * ring_parity_floats(h)) * sizeof(float);
-            const bool nt = working_set > kMallBytes / 2;
             L.fn = pick_tile(rule, h->pw, nt, h->d % 4 != 0);
             L.run_shift = run_shift_of(kPathTile, adam, h->d, nt);
             fn = (const void *)L.fn;
@@ -2994,7 +3006,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             break;
         }
         case kPathDTree:
-            L.fn2 = pick_dtree(rule, h->pw, h->d % 4 != 0);
+            L.fn2 = pick_dtree(rule, h->pw, nt, h->d % 4 != 0);
             fn = (const void *)L.fn2;
             lds = std::max(dtree_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
@@ -3005,11 +3017,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             lds = std::max(dtree_seq_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
         case kPathCluster: {
-            const size_t rows = 2 + (uses_s1 ? 1 : 0) + (adam ? 1 : 0);
-            const size_t working_set =
-                (rows * (size_t)h->n * (size_t)h->d + 2 * ring_parity_floats(h)) * sizeof(float);
-            if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, working_set > kMallBytes / 2,
-                              h->d % 4 != 0,
+            if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
                               h->d % 4 == 0, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
             L.run_shift = run_shift_of(kPathCluster, adam, h->d, true);

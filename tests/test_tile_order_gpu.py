@@ -34,6 +34,9 @@ CASES = [
     ("cluster", "hubs", 90, 33 * T - 16),      # hubs, a last run of 1 tile
     ("cluster", "random", 40, 5 * T + 1),      # fewer tiles than a run
     ("cluster", "chain", 48, 40 * T),          # rows of whole lines: no runs
+    ("dtree", "double", 16, 640 * T + 3),      # streaming: past half of the MALL
+    ("dtree", "double", 20, 520 * T),          # the same, two workers in some waves
+    ("dtree", "double", 16, 600 * T + 1),      # the largest that stay in the caches
     ("dtree_seq", "double", 33, 128 * T - 1),  # one cycle of 128 tiles exactly
     ("dtree_seq", "double", 40, 129 * T + 17),
     ("cluster_dtree", "double", 70, 50 * T + 3),
