@@ -1089,25 +1089,28 @@ __global__ void __launch_bounds__(1024) relaysum_cluster_kernel(RoundArgs a, Clu
 // ring, ascending, then the new state.  Runs
 // after relaysum_cluster_kernel, which has written every message, the
 // counters and nbar; x^(t) (eq. robust, Alg. 4) and y (Alg. 3) of these
-// workers are still unwritten.
-template <int C, int R>
+// workers are still unwritten.  C floats per thread: 16-byte chunks at 4-byte
+// alignment, with TAIL (d % 4 != 0) the last one float by float, or one float
+// where a grid of chunks would not fill the device (resolve_launch).
+template <int C, int R, bool TAIL>
 __global__ void __launch_bounds__(256) relaysum_cluster_fixup(RoundArgs a, ClusterArgs k) {
     using T = RuleOf<R>;
-    const bool ok[1] = {true};
+    const int64_t chunks = a.nchunks + (TAIL ? 1 : 0);   // the last one partial
     for (int b = blockIdx.y; b < k.nb; b += gridDim.y) {
         const int i = k.bnd[b];
         const int s0 = a.row_ptr[i];
         const int deg = a.row_ptr[i + 1] - s0;
         const int nbar = a.nbar_out[i];
         const int64_t smp = T::mean ? a.smp_next[i] : (int64_t)1;
-        for (int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; chunk < a.nchunks;
+        for (int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; chunk < chunks;
              chunk += (int64_t)gridDim.x * blockDim.x) {
             const int64_t off = chunk * C;
+            const int ok[1] = {TAIL && a.d - off < C ? (int)(a.d - off) : C};
             const int64_t row = (int64_t)i * a.d + off;
             lanev<1, C> xo = zero_lane<1, C>();
-            if constexpr (T::keeps_x) xo = load_lane<1, C>(a.x + row, 0, ok);
-            if constexpr (T::mean) xo = load_lane<1, C>(a.s1 + row, 0, ok);
-            lanev<1, C> acc = load_lane<1, C>(k.scratch + (int64_t)b * a.d + off, 0, ok);
+            if constexpr (T::keeps_x) xo = load_lane<1, C, true, TAIL>(a.x + row, 0, ok);
+            if constexpr (T::mean) xo = load_lane<1, C, true, TAIL>(a.s1 + row, 0, ok);
+            lanev<1, C> acc = load_lane<1, C, true, TAIL>(k.scratch + (int64_t)b * a.d + off, 0, ok);
             // Eight messages loaded before they are added, in order: a hub's
             // completion walks hundreds of them.
             int q = k.bfirst[b];
@@ -1115,16 +1118,16 @@ __global__ void __launch_bounds__(256) relaysum_cluster_fixup(RoundArgs a, Clust
                 lanev<1, C> m[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    m[j] = load_lane<1, C>(a.ring_next + ring_off(a, k.rpos[a.rev[s0 + q + j]], off), 0, ok);
+                    m[j] = load_lane<1, C, true, TAIL>(a.ring_next + ring_off(a, k.rpos[a.rev[s0 + q + j]], off), 0, ok);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc = add_lane<1, C>(acc, m[j]);
             }
             for (; q < deg; ++q)
                 acc = add_lane<1, C>(
-                    acc, load_lane<1, C>(a.ring_next + ring_off(a, k.rpos[a.rev[s0 + q]], off), 0, ok));
+                    acc, load_lane<1, C, true, TAIL>(a.ring_next + ring_off(a, k.rpos[a.rev[s0 + q]], off), 0, ok));
             const lanev<1, C> xn = new_state<R, 1, C>(a, acc, xo, nbar, smp);
-            if constexpr (T::mean) store_lane<1, C>(a.s1 + row, 0, ok, xo);
-            store_lane<1, C>(a.x + row, 0, ok, xn);
+            if constexpr (T::mean) store_lane<1, C, true, TAIL>(a.s1 + row, 0, ok, xo);
+            store_lane<1, C, true, TAIL>(a.x + row, 0, ok, xn);
         }
     }
 }
@@ -2384,25 +2387,26 @@ kernelc_fn cluster_for(bool low_degree, int pw) {
 }
 
 template <int R>
-void cluster_pair(bool low, int pw, bool nt, bool tail, bool c4, kernelc_fn *k1, kernelc_fn *k2) {
+void cluster_pair(bool low, int pw, bool nt, bool tail, bool wide, kernelc_fn *k1, kernelc_fn *k2) {
     if (tail) *k1 = nt ? cluster_for<R, true, true>(low, pw) : cluster_for<R, false, true>(low, pw);
     else *k1 = nt ? cluster_for<R, true, false>(low, pw) : cluster_for<R, false, false>(low, pw);
-    *k2 = c4 ? relaysum_cluster_fixup<4, R> : relaysum_cluster_fixup<1, R>;
+    if (!wide) *k2 = relaysum_cluster_fixup<1, R, false>;
+    else *k2 = tail ? relaysum_cluster_fixup<4, R, true> : relaysum_cluster_fixup<4, R, false>;
 }
 
-// Cluster kernel and boundary fixup of a rule; `tail` when d % 4 != 0, `c4`
-// when the fixup may move whole 16-byte chunks (d % 4 == 0).
-bool pick_cluster(int rule, bool low, int pw, bool nt, bool tail, bool c4, kernelc_fn *k1,
+// Cluster kernel and boundary fixup of a rule; `tail` when d % 4 != 0, `wide`
+// when the fixup moves 16-byte chunks.
+bool pick_cluster(int rule, bool low, int pw, bool nt, bool tail, bool wide, kernelc_fn *k1,
                   kernelc_fn *k2) {
     switch (rule) {
-        case kModelSgd: cluster_pair<kModelSgd>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kModelNesterov: cluster_pair<kModelNesterov>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kModelAdam: cluster_pair<kModelAdam>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kRobustSgd: cluster_pair<kRobustSgd>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kRobustNesterov: cluster_pair<kRobustNesterov>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kRobustAdam: cluster_pair<kRobustAdam>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kGrad: cluster_pair<kGrad>(low, pw, nt, tail, c4, k1, k2); return true;
-        case kMean: cluster_pair<kMean>(low, pw, nt, tail, c4, k1, k2); return true;
+        case kModelSgd: cluster_pair<kModelSgd>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kModelNesterov: cluster_pair<kModelNesterov>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kModelAdam: cluster_pair<kModelAdam>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kRobustSgd: cluster_pair<kRobustSgd>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kRobustNesterov: cluster_pair<kRobustNesterov>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kRobustAdam: cluster_pair<kRobustAdam>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kGrad: cluster_pair<kGrad>(low, pw, nt, tail, wide, k1, k2); return true;
+        case kMean: cluster_pair<kMean>(low, pw, nt, tail, wide, k1, k2); return true;
         default: return false;
     }
 }
@@ -2507,6 +2511,7 @@ struct relaysum_s {
         kernelc_fn fc1 = nullptr, fc2 = nullptr;
         kerneld_fn fd1 = nullptr, fd2 = nullptr;
         size_t lds = 0;
+        bool wide = true;        // cluster completion: 16-byte chunks, or single floats
         int32_t run_shift = 0;   // log2 of the neighbouring tiles on one XCD
         int32_t spill = 0;       // tile kernel with a spill sub-tile: its coordinates
         int64_t spill_grid = 0;  //   per workgroup, and the workgroups
@@ -3017,8 +3022,19 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             lds = std::max(dtree_seq_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
         case kPathCluster: {
+            // The completion of the boundary workers moves 16-byte chunks on
+            // any row once these fill the device (8 blocks of 256 threads per
+            // CU), one float per thread below that: a hub's thread walks
+            // hundreds of messages, and a quarter of the threads leaves CUs
+            // idle.  ms per round on MI355X, same box, one float | chunks:
+            // random tree of 1,000, d = 200,001 1.466 | 1.416; random 100,
+            // d = 2,000,003 1.541 | 1.516; 300 with hubs, Adam, d = 800,001
+            // 2.154 | 2.150; below the line 100 with hubs, eq. robust, d =
+            // 60,001 .066 | .072, random 50, d = 60,001 .0316 | .0324; on
+            // aligned rows, d = 60,000, .0603 | .0640 and .0310 | .0319.
+            L.wide = (h->d / 4 + 255) / 256 * (int64_t)h->cl_nb >= 8 * (int64_t)h->cu_count;
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
-                              h->d % 4 == 0, &L.fc1, &L.fc2))
+                              L.wide, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
             L.run_shift = run_shift_of(kPathCluster, adam, h->d, true);
             fn = (const void *)L.fc1;
@@ -3421,11 +3437,10 @@ int relaysum_step_ex(relaysum_t *h, float *x, const float *g, float *state1, flo
         hipError_t st = hipGetLastError();
         if (st != hipSuccess) return hip_fail(h, st, "cluster kernel launch");
         if (h->cl_nb > 0) {
-            // Boundary workers: C floats per thread, C = 4 when rows hold
-            // whole 16-byte chunks.
             RoundArgs b = a;
-            b.nchunks = h->d % 4 == 0 ? h->d / 4 : h->d;
-            const unsigned gx = (unsigned)std::min<int64_t>((b.nchunks + 255) / 256, 1024);
+            b.nchunks = L.wide ? h->d / 4 : h->d;   // whole chunks; a partial last one with d % 4 != 0
+            const int64_t chunks = L.wide ? (h->d + 3) / 4 : h->d;
+            const unsigned gx = (unsigned)std::min<int64_t>((chunks + 255) / 256, 1024);
             const unsigned gy = (unsigned)std::min<int64_t>(h->cl_nb, 65535);
             hipLaunchKernelGGL(L.fc2, dim3(gx, gy), dim3(256), 0, h->stream, b, k);
             st = hipGetLastError();
