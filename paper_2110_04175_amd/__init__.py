@@ -177,6 +177,14 @@ def _check_mask(t, slots):
                          "(one per directed-edge slot)")
 
 
+def _current_stream() -> int:
+    """Address of torch's current stream on the current device.  The raw
+    handle takes 0.2 us to read, a torch.cuda.Stream object for it 2.7 us,
+    out of a small round's 8.4 us."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 # ---- functions with the C names ---------------------------------------------
 
 
@@ -443,8 +451,7 @@ class RelaySum:
         _check_tensor(g, self.n, self.d, "g")
         _check_tensor(mom, self.n, self.d, "mom")
         if self._stream is None:
-            import torch
-            relaysum_set_stream(self.h, torch.cuda.current_stream())
+            relaysum_set_stream(self.h, _current_stream())
         relaysum_step(self.h, x, g, mom, lr, beta)
 
     def step_ex(self, x, g, state1=None, state2=None, **kw) -> None:
@@ -454,8 +461,7 @@ class RelaySum:
             _check_tensor(t, self.n, self.d, nm)
         _check_mask(kw.get("dropped"), self.num_directed_edges)
         if self._stream is None:
-            import torch
-            relaysum_set_stream(self.h, torch.cuda.current_stream())
+            relaysum_set_stream(self.h, _current_stream())
         relaysum_step_ex(self.h, x, g, state1, state2, **kw)
 
     def samples(self) -> np.ndarray:
@@ -465,8 +471,7 @@ class RelaySum:
         """(consensus distance, largest coordinate deviation) of the models x."""
         _check_tensor(x, self.n, self.d, "x")
         if self._stream is None:
-            import torch
-            relaysum_set_stream(self.h, torch.cuda.current_stream())
+            relaysum_set_stream(self.h, _current_stream())
         return relaysum_consensus_distance(self.h, x)
 
     def reset(self) -> None:
