@@ -722,8 +722,8 @@ __device__ __forceinline__ void cluster_of_workgroup(const RoundArgs &a, int cou
 
 // ---- tile kernel -------------------------------------------------------------
 
-// Workgroup b owns tile b, the 64*U*C consecutive coordinates starting at
-// b*64*U*C, for every row.
+// A workgroup owns one tile (xcd_run_place), 64*U*C consecutive coordinates
+// from a multiple of 64*U*C on, for every row.
 //
 // SP (spill): a grid of short rounds whose tiles exceed a whole number of
 // dispatch rounds (of the workgroups that fit on the device at once) by a
@@ -896,9 +896,9 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
 // ---- cluster kernels ------------------------------------------------------------
 
 // Trees of more than 32 workers cut into clusters: connected subtrees of at most
-// 16 workers (host: plan_clusters).  Workgroup b owns one 512-coordinate
-// tile of one cluster: cluster b mod K of tile b / K, so the K clusters of a
-// tile run on neighbouring workgroups.  Each wave owns one member.  Phase 1
+// 16 workers (host: plan_clusters).  A workgroup owns one 512-coordinate
+// tile of one cluster (cluster_of_workgroup): the K clusters of a tile, or of
+// a run of tiles, run on neighbouring workgroups.  Each wave owns one member.  Phase 1
 // is the tile kernel's for the members: payload, optimizer state, every
 // outgoing message to the ring, and the messages between members also to an
 // LDS tile (slot k.lslot[s] of the cluster).  Phase 2 completes the members
