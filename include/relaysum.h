@@ -231,8 +231,12 @@ int relaysum_get_samples(relaysum_t *h, int64_t *samples_host);
  * arrays.  Accumulated in binary64 in an order fixed by n and d, so equal
  * inputs give equal bits.  Queued on the handle's stream behind its rounds,
  * then the stream is synchronised (not for graph capture).  d == 0 gives 0
- * and 0.  A NaN in x makes *dist NaN.  Not part of a round: an observability
- * aid for training loops and tests. */
+ * and 0.  A NaN or an infinity in x makes *dist NaN.  *spread leaves out the
+ * deviations that are no numbers: a coordinate with a NaN or with infinities
+ * of both signs, and an infinite value's from the infinite mean; a coordinate
+ * where some workers' values are infinite, of one sign, and others' finite
+ * makes it infinite.  Not part of a round: an observability aid for training
+ * loops and tests. */
 int relaysum_consensus_distance(relaysum_t *h, const float *x, double *dist, double *spread);
 
 /* Back to the state before the first round: messages, counters and sample

@@ -2071,25 +2071,33 @@ int metric_groups(int32_t n) {
     return g;
 }
 
-// Mean and sum of squared deviations of a set of values, mergeable: two
-// sets' come together as Chan, Golub and LeVeque's pairwise update gives
-// them, so a set's values are read once and no square of a large mean
-// cancels.
+// Sum of a set of values and of their squared deviations from its mean,
+// mergeable: two sets' come together as Chan, Golub and LeVeque's pairwise
+// update gives them from the sums, so a set's values are read once and no
+// square of a large mean cancels.  Merging sums rather than means keeps two
+// things.  An infinity stays one whichever worker it comes from: a mean moved
+// by (t.mean - s.mean) * w turns it into a NaN at the next merge.  And the
+// difference below has no division in it: for models near one another the
+// sums and products of binary32 values are exact or nearly so, where a merged
+// mean's rounding, times the mean over the deviation, went into m2 (300
+// workers at 1e4 + N(0, 1e-3): relative errors of 4.5e-10 per coordinate
+// against 3e-16; two passes 8e-15).
 struct Spread {
-    double mean, m2;
+    double sum, m2;
 };
 
-// (s of `ca` values) with (t of `cb` values): w = cb/(ca+cb), c = ca*cb/(ca+cb).
-__device__ __forceinline__ void merge_spread(Spread &s, const Spread &t, double w, double c) {
-    const double e = t.mean - s.mean;
-    s.mean += e * w;
+// (s of `ca` values) with (t of `cb` values): c = 1 / (ca * cb * (ca + cb)),
+// or 0 for an empty s.
+__device__ __forceinline__ void merge_spread(Spread &s, const Spread &t, double ca, double cb, double c) {
+    const double e = ca * t.sum - cb * s.sum;
+    s.sum += t.sum;
     s.m2 += t.m2 + e * e * c;
 }
 
 // Stage 1.  A wave takes 256 coordinates (4 per lane, 16-byte accesses at
 // 4-byte alignment) of every worker, or of every G-th one where G waves
-// share a tile, 8 workers' values in registers at a time: their mean and
-// squared deviations from it in binary64, merged with those before; the G
+// share a tile, 8 workers' values in registers at a time: their sum and the
+// squared deviations from their mean in binary64, merged with those before; the G
 // waves' results merge through LDS.  Every value is read once (a
 // two-pass sum of one float per thread took 0.50 ms on 16 workers at d =
 // 9.75M; with this kernel the whole call, both stages and the 16-byte copy
@@ -2117,7 +2125,7 @@ __global__ void __launch_bounds__(512) relaysum_consensus_kernel(const float *x,
         float lo[4], hi[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            sp[k].mean = sp[k].m2 = 0.0;
+            sp[k].sum = sp[k].m2 = 0.0;
             lo[k] = __builtin_inff();
             hi[k] = -__builtin_inff();
         }
@@ -2131,25 +2139,25 @@ __global__ void __launch_bounds__(512) relaysum_consensus_kernel(const float *x,
                 if (j < nb)
                     v[j] = load_lane<1, 4, true, true>(x + (int64_t)(i0 + j * groups) * d + (c0 - lane * 4),
                                                        lane, ok);
-            const double ca = seen, cb = nb, w = cb / (ca + cb);
+            const double ca = seen, cb = nb, c = seen ? 1.0 / (ca * cb * (ca + cb)) : 0.0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 Spread b = {0.0, 0.0};
 #pragma unroll
                 for (int j = 0; j < kMetricBatch; ++j)
                     if (j < nb) {
-                        b.mean += (double)v[j].v[0][k];
+                        b.sum += (double)v[j].v[0][k];
                         lo[k] = fminf(lo[k], v[j].v[0][k]);
                         hi[k] = fmaxf(hi[k], v[j].v[0][k]);
                     }
-                b.mean /= cb;
+                const double mean = b.sum / cb;
 #pragma unroll
                 for (int j = 0; j < kMetricBatch; ++j)
                     if (j < nb) {
-                        const double e = (double)v[j].v[0][k] - b.mean;
+                        const double e = (double)v[j].v[0][k] - mean;
                         b.m2 += e * e;
                     }
-                merge_spread(sp[k], b, w, ca * w);
+                merge_spread(sp[k], b, ca, cb, c);
             }
             seen += nb;
         }
@@ -2166,10 +2174,10 @@ __global__ void __launch_bounds__(512) relaysum_consensus_kernel(const float *x,
             if (r == 0) {
                 for (int q = 1; q < groups; ++q) {
                     const int cq = (n - q + groups - 1) / groups;   // workers of wave q (n > groups)
-                    const double ca = seen, cb = cq, w = cb / (ca + cb);
+                    const double ca = seen, cb = cq, c = 1.0 / (ca * cb * (ca + cb));
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        merge_spread(sp[k], s_sp[(wave + q) * kMetricTile + k * kWave + lane], w, ca * w);
+                        merge_spread(sp[k], s_sp[(wave + q) * kMetricTile + k * kWave + lane], ca, cb, c);
                         lo[k] = fminf(lo[k], s_mm[(2 * (wave + q)) * kMetricTile + k * kWave + lane]);
                         hi[k] = fmaxf(hi[k], s_mm[(2 * (wave + q) + 1) * kMetricTile + k * kWave + lane]);
                     }
@@ -2182,7 +2190,8 @@ __global__ void __launch_bounds__(512) relaysum_consensus_kernel(const float *x,
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 acc += sp[k].m2;
-                mx = fmax(mx, fmax((double)hi[k] - sp[k].mean, sp[k].mean - (double)lo[k]));
+                const double mean = sp[k].sum / (double)n;
+                mx = fmax(mx, fmax((double)hi[k] - mean, mean - (double)lo[k]));
             }
         }
     }

@@ -109,3 +109,50 @@ def test_worker_groups_and_tile_edges(n, d, offset):
         xd[n // 2, d - 1] = float("nan")
         dist, spread = h.consensus_distance(xd)
         assert np.isnan(dist) and abs(spread - consensus_distance(x[:, :-1])[1]) <= 1e-10 * want_spread
+
+
+@pytest.mark.parametrize("n", [2, 8, 9, 16, 33, 64, 65, 200, 1_003])
+def test_infinities(n):
+    """A worker whose model ran off to an infinity shows as an infinite spread
+    whichever worker it is: in the first, a middle and the last batch of 8 and
+    wave of a tile.  Deviations that are no numbers are left out, as a maximum
+    over the oracle's deviations without its NaNs has them: with infinities of
+    both signs, with a NaN beside one, and where every worker's value is
+    infinite."""
+    announce(f"consensus distance with infinities n={n}")
+    d, inf, nan = 301, float("inf"), float("nan")
+    base = np.random.default_rng(n).standard_normal((n, d)).astype(np.float32)
+    last = n - 1
+    plants = [[(w, c, v)] for w in sorted({0, 7 % n, n // 2, last}) for c, v in ((5, inf), (d - 1, -inf))]
+    plants += [[(0, 9, inf), (last, 9, inf)], [(0, 9, inf), (last, 9, -inf)], [(0, 9, nan), (last, 9, inf)],
+               [(0, 9, inf), (last, 9, nan)], [(w, 9, inf) for w in range(n)],
+               [(0, 2, nan), (last, d - 1, inf)]]
+    with rs.RelaySum(n, d, wl.chain_edges(n)) as h:
+        for plant in plants:
+            x = base.copy()
+            for w, c, v in plant:
+                x[w, c] = v
+            x64 = x.astype(np.float64)
+            with np.errstate(invalid="ignore"):
+                want = np.fmax.reduce(np.abs(x64 - x64.sum(axis=0) / n), axis=None)
+            dist, spread = h.consensus_distance(torch.from_numpy(x).cuda())
+            assert np.isnan(dist), plant
+            # Finite: one subtraction from a mean of n values of a few units.
+            assert spread == want or abs(spread - want) <= n * 2.0**-50, (plant, spread, want)
+
+
+@pytest.mark.parametrize("n", [16, 33, 65, 300, 1_003])
+@pytest.mark.parametrize("scale", [100.0, 1e4])
+def test_precision_far_from_zero(n, scale):
+    """Models close together and far from zero, few coordinates so that their
+    errors don't average out.  Bound: either side adds n squares, each rounded
+    twice; a mean off by a rounding counts by its square.  So (n + 4) * 2^-53
+    on each side, and twice that between them."""
+    announce(f"consensus distance precision n={n} scale={scale}")
+    d = 3
+    for seed in range(4):
+        x = (scale + 1e-3 * np.random.default_rng(seed).standard_normal((n, d))).astype(np.float32)
+        with rs.RelaySum(n, d, wl.chain_edges(n)) as h:
+            dist, _ = h.consensus_distance(torch.from_numpy(x).cuda())
+        want, _ = consensus_distance(x)
+        assert abs(dist - want) <= (n + 4) * 2.0**-52 * want, (seed, dist, want, abs(dist / want - 1))
