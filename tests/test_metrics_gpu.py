@@ -31,9 +31,9 @@ def _rows(n, d, offset, seed):
 @pytest.mark.parametrize("n,d,offset", [(16, 1_001, 0), (5, 3, 1), (1, 700, 0), (300, 4_099, 2),
                                         (16, 2_000_001, 1)])
 def test_matches_the_oracle(n, d, offset):
-    """Several grid widths: fewer coordinates than one block's threads, a
-    ragged tail, one worker, and more coordinates than the 1,024 blocks
-    cover in one pass; rows 4 bytes off alignment."""
+    """Several grid widths: less than one tile of 256 coordinates, a ragged
+    tail, one worker, and most of a full grid (1,954 of at most 2,048 blocks,
+    a partial last one); rows 4 bytes off alignment."""
     announce(f"consensus distance n={n} d={d} offset={offset}")
     x, xd = _rows(n, d, offset, seed=n + d)
     with rs.RelaySum(n, d, wl.chain_edges(n)) as h:
@@ -88,7 +88,7 @@ def test_worker_groups_and_tile_edges(n, d, offset):
     """Where the work splits: one, two, four and eight waves to a tile of 256
     coordinates (up to 32, 64, 128 and more workers), whole and partial
     batches of 8 workers, whole tiles, partial last ones and partial last
-    16-byte chunks, and more tiles than blocks with waves sharing a tile.
+    16-byte chunks, and about 1,000 blocks of two tiles.
     Models far from zero with small deviations: 100 plus N(0, 1e-3), whose
     squares' difference would cancel.  Bound: each deviation carries a few
     2^-53 of the mean over deviations of 1e-3, about 1e5 times smaller than
@@ -156,3 +156,29 @@ def test_precision_far_from_zero(n, scale):
             dist, _ = h.consensus_distance(torch.from_numpy(x).cuda())
         want, _ = consensus_distance(x)
         assert abs(dist - want) <= (n + 4) * 2.0**-52 * want, (seed, dist, want, abs(dist / want - 1))
+
+
+@pytest.mark.parametrize("n,d,offset,tiles_per_block", [
+    (3, 2_100_001, 0, 4), (16, 4_194_305, 1, 4), (33, 1_050_002, 1, 2), (65, 530_002, 2, 1),
+    (129, 530_001, 3, 1), (129, 1_048_577, 0, 1)])
+def test_blocks_that_loop(n, d, offset, tiles_per_block):
+    """More tiles than one pass of the 2,048 blocks takes, for one, two, four
+    and eight waves to a tile: some blocks, and all of them, go on to further
+    tiles, reusing the memory through which the waves of a tile meet; the last
+    pass is ragged.  The largest deviation sits in the first pass, then in the
+    last.  Bound: binary64 sums of about 1e8 terms."""
+    announce(f"consensus distance, looping blocks n={n} d={d} offset={offset}")
+    tiles = -(-d // 256)
+    assert -(-tiles // tiles_per_block) > 2_048
+    x, xd = _rows(n, d, offset, seed=n + d)
+    want, _ = consensus_distance(x)
+    with rs.RelaySum(n, d, wl.chain_edges(n)) as h:
+        dist, spread = h.consensus_distance(xd)
+        assert abs(dist - want) <= 1e-12 * want, (dist, want)
+        for c in (17, d - 1):
+            keep = x[n - 1, c]
+            x[n - 1, c] = xd[n - 1, c] = 1e3
+            _, spread = h.consensus_distance(xd)
+            _, want_spread = consensus_distance(x[:, c:c + 1])
+            assert abs(spread - want_spread) <= 1e-12 * want_spread, (c, spread, want_spread)
+            x[n - 1, c] = xd[n - 1, c] = float(keep)
