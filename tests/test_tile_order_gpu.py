@@ -28,6 +28,11 @@ CASES = [
     ("tile", "chain", 16, 640 * T + 1),        # one tile past them
     ("tile", "heap", 16, 671 * T + 16),        # pairs, 42 cycles of 16
     ("tile", "chain", 20, 639 * T + 5),        # two workers in some waves, inside a cycle
+    # 124 KB of messages, one workgroup per CU: 512 workgroups in two dispatch
+    # rounds of 256, the excess over 512 tiles as spill coordinates, whose
+    # owners are in launch order beside tiles in runs of 8 and in pairs.
+    ("tile", "chain", 32, 270_001),
+    ("tile", "chain", 32, 270_000),
     ("cluster", "chain", 40, 36 * T + 3),      # shorter than one cycle
     ("cluster", "chain", 64, 32 * T - 1),      # 32 tiles of 4 clusters: one cycle exactly
     ("cluster", "random", 100, 50 * T + 7),    # a last run of 3 tiles
