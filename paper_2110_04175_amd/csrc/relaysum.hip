@@ -686,8 +686,8 @@ __device__ __forceinline__ void emit_messages(const RoundArgs &a, float *s_msg, 
     }
 }
 
-// Place of this workgroup, b, in the order of the tiles (run_shift_of says
-// which launches group how many).  Workgroups go to the eight
+// Place of this workgroup, b, in the order of the tiles (tile_run_shift and
+// cluster_run_shift say which launches group how many).  Workgroups go to the eight
 // XCDs round robin (workgroup b to XCD b mod 8), each with its own L2; with
 // `shift` the places 2^shift * k .. 2^shift * (k + 1) - 1 go to one XCD
 // (workgroups b, b + 8, .. of each group of 8 * 2^shift, dispatched close
@@ -1249,7 +1249,7 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int64_t tile = xcd_run_place(a.run_shift);
+    const int64_t tile = blockIdx.x;
     const int64_t base = tile * (64 * U * 4);   // model coordinate of the tile
     const int64_t tbase = tile * kSlot;         // carried coordinate in each tree
     int ok[U];   // valid model coordinates in each of the lane's chunks
@@ -2098,11 +2098,12 @@ __device__ __forceinline__ void merge_spread(Spread &s, const Spread &t, double 
 // 4-byte alignment) of every worker, or of every G-th one where G waves
 // share a tile, 8 workers' values in registers at a time: their sum and the
 // squared deviations from their mean in binary64, merged with those before; the G
-// waves' results merge through LDS.  Every value is read once (a
-// two-pass sum of one float per thread took 0.50 ms on 16 workers at d =
-// 9.75M; with this kernel the whole call, both stages and the 16-byte copy
-// to the host, went from 615 to 135 us, 4.6 TB/s), and the largest deviation comes from the coordinate's
-// extremes, as subtraction is monotone.  The order is fixed by n and d.
+// waves' results merge through LDS.  Every value is read once (two passes of
+// one float per thread and a serial last sum took 616 us a call on 16 workers
+// at d = 9.75M; this kernel, the parallel last sum and its pinned result take
+// 125 us, 5.0 TB/s over the whole call), and the largest deviation comes from
+// the coordinate's extremes, as subtraction is monotone.  The order is fixed
+// by n and d.
 // part[2b] = sum, part[2b+1] = max of block b.
 __global__ void __launch_bounds__(512) relaysum_consensus_kernel(const float *x, int32_t n, int64_t d,
                                                                  int groups, double *part) {
@@ -2889,44 +2890,53 @@ static bool locate_slot(const relaysum_t *h, int32_t slot, int *tree, int32_t *l
 // aligned rows.
 enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kPathClusterDTree };
 
-// log2 of the neighbouring tiles that one XCD takes (xcd_run_place) on a path
-// with rows of d floats; `streams`: a round past the caches.
+// log2 of the neighbouring tiles that one XCD takes (xcd_run_place).
 //
 // Two neighbouring tiles share a line of every row that does not start on
 // one (row i starts i*d*4 bytes into its array).  On two XCDs that line is
 // read from memory twice and written as two partial lines; on one XCD, by
 // workgroups dispatched close together, its L2 joins them.  Memory takes
 // partial 64-byte blocks dearest, so rows with d % 16 != 0 gain most from
-// long runs, and rows of whole 128-byte lines (d % 32 == 0) nothing.  ms per
-// round on MI355X, same box, runs of 1 | 2 | 8 | 16 tiles:
-//   tile kernel   chain of 16, d = 9.75M        .922 | .915 | .917 | .923
-//                 the same, d = 9,750,001       .993 | .976 | .971 | .975
-//                 the same, Adam               1.265 | 1.307 | 1.243 | 1.247
-//                 Adam, d = 9.75M              1.180 | 1.215 | 1.199 | 1.200
-//   cluster       chain of 64, d = 9.75M       4.134 | 4.176 | 4.128 | 4.087
-//                 2,000 with hubs, d = 150,000 2.203 | 2.178 | 2.117 | 2.103
-//                 random 1,000, d = 200,001    1.571 | 1.537 | 1.487 | 1.479
-//                 random 256, d = 1M           1.711 | 1.728 | 1.702 | 1.717
+// long runs, and rows of whole 128-byte lines (d % 32 == 0) little or less
+// than nothing.  us per round on MI355X, runs of 1 | 2 | 8 | 16 tiles, timed in
+// turn on the same arrays (medians of 15, which repeat within 0.5%; Adam 1%):
+//   tile kernel   chain of 16, d = 9.75M         925 |  920 |  918 |
+//                 the same, no momentum          703 |  696 |  699 |
+//                 d = 9,750,016 (whole lines)    897 |  910 |  907 |
+//                 d = 9,750,001                  983 |  972 |  970 |  974
+//                 random 24, d = 2,000,003       322 |  317 |  318 |  318
+//                 Adam, d = 9,750,001           1270 | 1310 | 1244 | 1246
+//                 Adam, d = 9.75M               1192 | 1211 | 1176 |
+//   cluster       chain of 64, d = 9.75M        4133 | 4149 | 4116 | 4071
+//                 2,000 with hubs, d = 150,000  2209 | 2185 | 2128 | 2108
+//                 random 1,000, d = 200,001     1503 | 1473 | 1424 | 1419
+//                 random 256, d = 1,000,016     1716 | 1709 | 1687 | 1701
+//                 random 256, d = 1M (lines)    1690 | 1698 | 1679 | 1694
+//   in the caches chain of 40, d = 60,001       23.7 |      | 23.3 | 23.9
+//                 random 300, d = 5,003         23.7 |      | 23.1 | 23.4
 //   double trees, one after the other
-//                 64, d = 9.75M                4.092 | 4.388 | 4.038 | 3.982
-//                 40, d = 4M                    .976 | 1.000 | 1.002 | .984
-// Pairs on the first row cut FETCH_SIZE from 3.101 to 3.074 GB.  Runs of 32
-// and 64 tiles were no faster.  Rounds that stay in the caches find the line
-// there (equal to 1%), and the double-tree kernel with both trees in LDS was
-// slower with every run (16 workers, d = 9.75M: .889 | .925 | .898 | .899).
-static int run_shift_of(Path path, bool adam, int64_t d, bool streams) {
-    switch (path) {
-        case kPathTile:
-            if (!streams) return 0;
-            return d % 16 != 0 ? 3 : adam ? 0 : 1;
-        case kPathDTreeSeq:
-        case kPathCluster:
-        case kPathClusterDTree:
-            return d % 32 != 0 ? 4 : 0;
-        default:
-            return 0;
-    }
+//                 64, d = 9.75M                 4046 | 4472 | 3998 | 3950
+//                 40, d = 4,000,001             1055 |      | 1051 | 1028
+//                 40, d = 4M (lines)             974 |      | 1006 |  981
+//   in clusters   200, d = 1,000,016            1316 | 1308 | 1309 | 1303
+//                 100, d = 100,001              90.7 |      | 89.0 | 89.3
+// Runs of 32 and 64 tiles were no faster.  The double-tree kernel with both
+// trees in LDS was slower with every run (16 workers, d = 9.75M, ms: .889 |
+// .925 | .898 | .899) and owns its tiles in launch order.  The rule looks at d
+// alone.  Arrays that start off a line have every row off it whatever d is,
+// and would gain as rows of odd length do: 4 bytes off, the chain of 16 at d =
+// 9,750,016 takes 976 | 961 | 953, the random tree of 256 at d = 1M 1881 |
+// | 1772 | 1772.
+
+// The tile kernel.  Rounds that stay in the caches (`nt` false) find the
+// shared lines there: equal to 1%.
+static int tile_run_shift(bool adam, int64_t d, bool nt) {
+    if (!nt) return 0;
+    return d % 16 != 0 ? 3 : adam ? 0 : 1;
 }
+
+// The cluster kernels and the sequential double-tree kernel, short rounds too.
+static int cluster_run_shift(int64_t d) { return d % 32 != 0 ? 4 : 0; }
 
 static Path path_of(const relaysum_t *h) {
     if (h->tile && h->ntrees == 1) return kPathTile;
@@ -2977,7 +2987,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
     switch (path_of(h)) {
         case kPathTile: {
             L.fn = pick_tile(rule, h->pw, nt, h->d % 4 != 0);
-            L.run_shift = run_shift_of(kPathTile, adam, h->d, nt);
+            L.run_shift = tile_run_shift(adam, h->d, nt);
             fn = (const void *)L.fn;
             const int floats_per_lane = 4 * kU4;
             lds = std::max(tile_lds_bytes(h->n, h->tr[0].e2, floats_per_lane, mean), cap_lds);
@@ -3031,7 +3041,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             break;
         case kPathDTreeSeq:
             L.fn2 = pick_dtree_seq(rule, h->pw, h->d % 4 != 0);
-            L.run_shift = run_shift_of(kPathDTreeSeq, adam, h->d, true);
+            L.run_shift = cluster_run_shift(h->d);
             fn = (const void *)L.fn2;
             lds = std::max(dtree_seq_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
@@ -3050,7 +3060,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
                               L.wide, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
-            L.run_shift = run_shift_of(kPathCluster, adam, h->d, true);
+            L.run_shift = cluster_run_shift(h->d);
             fn = (const void *)L.fc1;
             lds = cluster_lds_bytes(h->n, h->tr[0].e2, h->cl_slots[0], mean, h->cl_relay);
             if (h->cl_relay) lds = std::max(lds, cap_lds);
@@ -3059,7 +3069,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
         case kPathClusterDTree:
             if (!pick_cluster_dtree(rule, h->d % 4 != 0, h->cl_cap / kMaxWaves, &L.fd1, &L.fd2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
-            L.run_shift = run_shift_of(kPathClusterDTree, adam, h->d, true);
+            L.run_shift = cluster_run_shift(h->d);
             fn = (const void *)L.fd1;
             // Both trees' message tiles of the largest cluster; no residency cap.
             lds = ((size_t)h->cl_slots[0] + h->cl_slots[1]) * kWave * kDTreeU * 2 * sizeof(float);
@@ -4159,7 +4169,7 @@ extern "C" int relaysum_step_static(int32_t n, int64_t d, const int32_t *edges, 
     a.d = d;
     a.nchunks = d / 4;
     a.ntiles = ntiles;
-    a.run_shift = run_shift_of(kPathTile, false, d, nt);
+    a.run_shift = tile_run_shift(false, d, nt);
     a.cnt_prev = cnt + (size_t)prev * e2;
     a.cnt_next = cnt + (size_t)next * e2;
     a.nbar_out = cnt + 2 * (size_t)e2;
