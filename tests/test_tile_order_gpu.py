@@ -21,8 +21,9 @@ pytestmark = pytest.mark.gpu
 T = 512   # coordinates of a tile
 
 # path, tree, n, d.  Tile kernel: past half of the MALL (432*d bytes at 16
-# workers), runs of 8 for d % 16 != 0 and pairs otherwise.  The others: runs
-# of 16 for d % 32 != 0, by 1 otherwise.
+# workers), runs of 8 for d % 16 != 0 and pairs otherwise.  The cluster
+# kernels and dtree_seq: runs of 16 for d % 32 != 0, by 1 otherwise.  dtree:
+# launch order, here on both sides of the cache-allocating accesses.
 CASES = [
     ("tile", "chain", 16, 640 * T - 1),        # ten cycles of 64 tiles exactly
     ("tile", "chain", 16, 640 * T + 1),        # one tile past them
@@ -41,7 +42,7 @@ CASES = [
     ("cluster", "chain", 48, 40 * T),          # rows of whole lines: no runs
     ("dtree", "double", 16, 640 * T + 3),      # streaming: past half of the MALL
     ("dtree", "double", 20, 520 * T),          # the same, two workers in some waves
-    ("dtree", "double", 16, 600 * T + 1),      # the largest that stay in the caches
+    ("dtree", "double", 16, 600 * T + 1),      # near the largest that stay in the caches
     ("dtree_seq", "double", 33, 128 * T - 1),  # one cycle of 128 tiles exactly
     ("dtree_seq", "double", 40, 129 * T + 17),
     ("cluster_dtree", "double", 70, 50 * T + 3),
