@@ -2915,8 +2915,6 @@ enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kP
 //                 random 1,000, d = 200,001     1503 | 1473 | 1424 | 1419
 //                 random 256, d = 1,000,016     1716 | 1709 | 1687 | 1701
 //                 random 256, d = 1M (lines)    1690 | 1698 | 1679 | 1694
-//   in the caches chain of 40, d = 60,001       23.7 |      | 23.3 | 23.9
-//                 random 300, d = 5,003         23.7 |      | 23.1 | 23.4
 //   double trees, one after the other
 //                 64, d = 9.75M                 4046 | 4472 | 3998 | 3950
 //                 40, d = 4,000,001             1055 |      | 1051 | 1028
@@ -2938,8 +2936,33 @@ static int tile_run_shift(bool adam, int64_t d, bool nt) {
     return d % 16 != 0 ? 3 : adam ? 0 : 1;
 }
 
-// The cluster kernels and the sequential double-tree kernel, short rounds too.
-static int cluster_run_shift(int64_t d) { return d % 32 != 0 ? 4 : 0; }
+// The cluster kernels and the sequential double-tree kernel, in the caches
+// too.  `workgroups` of `count` clusters.
+//
+// A run keeps one XCD on one cluster, and clusters differ in size, so a grid
+// of a few workgroups per CU (one at a time fits) ends with a whole dispatch
+// round of the large ones where launch order fills the slots that the small
+// ones leave.  Below 3 workgroups per CU, us per round, runs of 1 | 8 | 16:
+//   single trees  chain of 40, d = 45,557        20.6 | 19.8 | 20.9
+//                 100 with hubs, d = 38,389      47.1 | 48.1 | 50.9
+//                 random 300, d = 17,003         50.0 | 48.7 | 50.2
+//                 random 1,000, d = 7,001        67.2 | 64.8 | 66.9
+//                 chain of 64, d = 67,061        39.1 | 36.8 | 37.5
+//   double trees  70 (3 clusters), d = 50,001    38.5 | 38.6 | 44.8
+//                 130 (5), d = 27,637            39.1 | 46.0 | 45.9
+//                 200 (7), d = 20,001            42.1 | 47.9 | 47.3
+//                 100 (4), d = 67,061            68.3 | 66.7 | 66.8
+//                 256 (8), d = 18,421            50.5 | 50.1 | 49.6
+// With 4, 8, .. clusters launch order leaves an XCD to one or two of them
+// anyway, so double trees keep their runs there.  From 3 workgroups per CU on
+// runs of 16 are the best or within 1% of it but for a last round of 70
+// workers (d = 176,629, 4.04 workgroups per CU: 98.7 | 98.8 | 102.3).
+static int cluster_run_shift(Path path, int64_t d, int64_t workgroups, int count, int cu_count) {
+    if (d % 32 == 0) return 0;
+    if (path == kPathDTreeSeq || workgroups >= 3 * (int64_t)cu_count) return 4;
+    if (path == kPathCluster) return 3;
+    return count % 4 == 0 ? 4 : 0;
+}
 
 static Path path_of(const relaysum_t *h) {
     if (h->tile && h->ntrees == 1) return kPathTile;
@@ -3044,7 +3067,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             break;
         case kPathDTreeSeq:
             L.fn2 = pick_dtree_seq(rule, h->pw, h->d % 4 != 0);
-            L.run_shift = cluster_run_shift(h->d);
+            L.run_shift = cluster_run_shift(kPathDTreeSeq, h->d, grid_tiles, 1, h->cu_count);
             fn = (const void *)L.fn2;
             lds = std::max(dtree_seq_lds_bytes(h->n, h->tr[0].e2, h->tr[1].e2), cap_lds);
             break;
@@ -3063,7 +3086,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
                               L.wide, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
-            L.run_shift = cluster_run_shift(h->d);
+            L.run_shift = cluster_run_shift(kPathCluster, h->d, grid_tiles, h->cl_count, h->cu_count);
             fn = (const void *)L.fc1;
             lds = cluster_lds_bytes(h->n, h->tr[0].e2, h->cl_slots[0], mean, h->cl_relay);
             if (h->cl_relay) lds = std::max(lds, cap_lds);
@@ -3072,7 +3095,7 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
         case kPathClusterDTree:
             if (!pick_cluster_dtree(rule, h->d % 4 != 0, h->cl_cap / kMaxWaves, &L.fd1, &L.fd2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");
-            L.run_shift = cluster_run_shift(h->d);
+            L.run_shift = cluster_run_shift(kPathClusterDTree, h->d, grid_tiles, h->cl_count, h->cu_count);
             fn = (const void *)L.fd1;
             // Both trees' message tiles of the largest cluster; no residency cap.
             lds = ((size_t)h->cl_slots[0] + h->cl_slots[1]) * kWave * kDTreeU * 2 * sizeof(float);

@@ -22,8 +22,10 @@ T = 512   # coordinates of a tile
 
 # path, tree, n, d.  Tile kernel: past half of the MALL (432*d bytes at 16
 # workers), runs of 8 for d % 16 != 0 and pairs otherwise.  The cluster
-# kernels and dtree_seq: runs of 16 for d % 32 != 0, by 1 otherwise.  dtree:
-# launch order, here on both sides of the cache-allocating accesses.
+# kernels and dtree_seq for d % 32 != 0: runs of 16, but below 3 workgroups per
+# CU runs of 8 on single trees and launch order on double trees whose number of
+# clusters is no multiple of 4; by 1 otherwise.  dtree: launch order, here on
+# both sides of the cache-allocating accesses.
 CASES = [
     ("tile", "chain", 16, 640 * T - 1),        # ten cycles of 64 tiles exactly
     ("tile", "chain", 16, 640 * T + 1),        # one tile past them
@@ -34,9 +36,13 @@ CASES = [
     # owners are in launch order beside tiles in runs of 8 and in pairs.
     ("tile", "chain", 32, 270_001),
     ("tile", "chain", 32, 270_000),
-    ("cluster", "chain", 40, 36 * T + 3),      # shorter than one cycle
-    ("cluster", "chain", 64, 32 * T - 1),      # 32 tiles of 4 clusters: one cycle exactly
+    ("cluster", "chain", 40, 36 * T + 3),      # runs of 8, inside a cycle of 8 * 8
+    ("cluster", "chain", 64, 32 * T - 1),      # 32 tiles of 4 clusters: two cycles exactly
     ("cluster", "random", 100, 50 * T + 7),    # a last run of 3 tiles
+    ("cluster", "chain", 64, 192 * T - 1),     # 3 workgroups per CU: runs of 16, six cycles of 8 * 16
+    ("cluster", "chain", 64, 191 * T - 1),     # the longest in runs of 8
+    ("cluster", "random", 100, 97 * T - 7),    # runs of 16, a last run of 1 tile
+    ("cluster", "hubs", 90, 142 * T + 5),      # the same with hubs, a last run of 15 tiles
     ("cluster", "hubs", 90, 33 * T - 16),      # hubs, a last run of 1 tile
     ("cluster", "random", 40, 5 * T + 1),      # fewer tiles than a run
     ("cluster", "chain", 48, 40 * T),          # rows of whole lines: no runs
@@ -45,8 +51,9 @@ CASES = [
     ("dtree", "double", 16, 600 * T + 1),      # near the largest that stay in the caches
     ("dtree_seq", "double", 33, 128 * T - 1),  # one cycle of 128 tiles exactly
     ("dtree_seq", "double", 40, 129 * T + 17),
-    ("cluster_dtree", "double", 70, 50 * T + 3),
-    ("cluster_dtree", "double", 100, 16 * T + 8),   # a last run of 1 tile
+    ("cluster_dtree", "double", 70, 50 * T + 3),    # 3 clusters: launch order
+    ("cluster_dtree", "double", 70, 256 * T + 1),   # 3 workgroups per CU: runs of 16, a last run of 1 tile
+    ("cluster_dtree", "double", 100, 16 * T + 8),   # 4 clusters: runs of 16, a last run of 1 tile
 ]
 
 
