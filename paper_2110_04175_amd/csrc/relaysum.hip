@@ -3073,16 +3073,27 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             break;
         case kPathCluster: {
             // The completion of the boundary workers moves 16-byte chunks on
-            // any row once these fill the device (8 blocks of 256 threads per
-            // CU), one float per thread below that: a hub's thread walks
-            // hundreds of messages, and a quarter of the threads leaves CUs
-            // idle.  ms per round on MI355X, same box, one float | chunks:
-            // random tree of 1,000, d = 200,001 1.466 | 1.416; random 100,
-            // d = 2,000,003 1.541 | 1.516; 300 with hubs, Adam, d = 800,001
-            // 2.154 | 2.150; below the line 100 with hubs, eq. robust, d =
-            // 60,001 .066 | .072, random 50, d = 60,001 .0316 | .0324; on
-            // aligned rows, d = 60,000, .0603 | .0640 and .0310 | .0319.
-            L.wide = (h->d / 4 + 255) / 256 * (int64_t)h->cl_nb >= 8 * (int64_t)h->cu_count;
+            // any row once these fill the device, one float per thread below
+            // that: a quarter of the threads leaves CUs idle.  The line is 5
+            // blocks of 256 threads per CU, and 8 with hubs, whose threads
+            // each walk a hub's messages.  us per round on MI355X, timed in
+            // turn, one float | chunks, at blocks of chunks per CU:
+            //   chain of 64, d = 288,000            6.6   127.4 | 125.7
+            //   chain of 256, d = 64,000            7.4   121.3 | 119.1
+            //   balanced tree of 100, d = 192,000   6.6   131.2 | 129.0
+            //   random 1,000, d = 10,240            5.2    85.0 |  84.1
+            //   random 100, d = 100,001             5.4    89.0 |  88.8
+            //   random 300, d = 32,001              4.4    81.1 |  81.7
+            //   random 100, d = 64,000              3.5    55.6 |  56.7
+            //   balanced tree of 100, d = 64,000    2.2    48.1 |  49.3
+            //   hubs 300, d = 160,768               8.0   343.2 | 341.7
+            //   hubs 600, d = 76,801                7.6   355.1 | 357.8
+            //   hubs 100, d = 240,001               5.5   181.8 | 184.6
+            //   hubs 2,000, d = 6,400               2.1   143.7 | 150.3
+            // (2,000 workers with hubs gain from single floats up to 16:
+            // d = 53,225 816 | 824.)
+            L.wide = (h->d / 4 + 255) / 256 * (int64_t)h->cl_nb >=
+                     (h->cl_hubs ? 8 : 5) * (int64_t)h->cu_count;
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
                               L.wide, &L.fc1, &L.fc2))
                 return fail(h, RELAYSUM_ERR_INVALID_ARG, "no cluster kernel for this rule");

@@ -17,15 +17,19 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("tree,n,d,offset,update", [
-    # Chunks: a random tree of 1,000 workers has over 100 boundary workers, 8
-    # blocks per CU from about 20,000 coordinates on.
+    # Chunks: a random tree of 1,000 workers has 134 boundary workers, 5 blocks
+    # of 1,024 coordinates per CU from about 9,800 coordinates on; 600 workers
+    # with hubs have 26, 8 blocks per CU from about 80,000.
     ("random", 1000, 30_720, 0, "model"),
     ("random", 1000, 30_721, 0, "model"),
     ("random", 1000, 30_722, 1, "robust"),
     ("random", 1000, 30_719, 3, "mean"),
+    ("random", 1000, 10_243, 0, "model"),
+    ("hubs", 600, 80_897, 0, "grad"),
+    ("hubs", 600, 80_898, 2, "model"),
+    # Single floats, on rows of whole chunks too.
     ("hubs", 600, 61_441, 0, "grad"),
     ("hubs", 600, 61_440, 2, "model"),
-    # Single floats, on rows of whole chunks too.
     ("random", 300, 1_024, 0, "model"),
     ("hubs", 100, 4_000, 0, "robust"),
     ("chain", 40, 3, 0, "model"),
