@@ -280,20 +280,40 @@ __device__ __forceinline__ void store_float(float *p, float v) {
 // and with TAIL also fewer in the chunk holding the row's last coordinates
 // when d % C != 0.  Whole chunks move as one access, the tail float by float.
 // Without TAIL the code is that of the bool-mask form.
+//
+// With TAIL a chunk stays one vector up to its last assignment, and the tail
+// is a second step rather than the other branch.  Merged float by float, some
+// of a chunk's floats ended in registers of their own, copied right behind
+// the load, and each copy waits for every load in flight: up to four of a
+// worker's rows came one after the other.  us per round on MI355X, before |
+// after: chain of 3, SGD, d = 20,000,001 339 | 284; balanced tree of 8, Adam,
+// d = 3,000,001 206 | 189; chain of 16, d = 1,250,001 128 | 125; double trees
+// of 2, SGD, d = 20,000,001 144 | 115.  In the caches a few rounds lose (double
+// trees of 12, d = 166,667 14.4 | 15.2), most gain (balanced tree of 8, d =
+// 12,501 7.1 | 6.4).
 template <int U, int C, bool NT, bool TAIL>
 __device__ __forceinline__ lanev<U, C> load_lane(const float *row, int lane, const int (&nv)[U]) {
     lanev<U, C> r;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const float *p = row + (u * 64 + lane) * C;
-        if (nv[u] == C) {
+        if constexpr (TAIL && C == 4) {
+            f4_t t = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (nv[u] == C) {
+                const f4u_t *q = reinterpret_cast<const f4u_t *>(p);
+                t = NT ? __builtin_nontemporal_load(q) : *q;
+            }
+            if (nv[u] > 0 && nv[u] < C) {
+                t.x = load_float<NT>(p);
+                if (nv[u] > 1) t.y = load_float<NT>(p + 1);
+                if (nv[u] > 2) t.z = load_float<NT>(p + 2);
+            }
+            r.v[u][0] = t.x; r.v[u][1] = t.y; r.v[u][2] = t.z; r.v[u][3] = t.w;
+        } else if (nv[u] == C) {
             load_chunk<C, NT>(p, r.v[u]);
-        } else if constexpr (TAIL) {
-#pragma unroll
-            for (int k = 0; k < C; ++k) r.v[u][k] = k < nv[u] ? load_float<NT>(p + k) : 0.0f;
         } else {
 #pragma unroll
-            for (int k = 0; k < C; ++k) r.v[u][k] = 0.0f;
+            for (int k = 0; k < C; ++k) r.v[u][k] = TAIL && k < nv[u] ? load_float<NT>(p + k) : 0.0f;
         }
     }
     return r;
@@ -537,7 +557,12 @@ __device__ __forceinline__ lanev<U, C> payload(const RoundArgs &a, const lanev<U
         for (int k = 0; k < C; ++k) {
             const float gv = g.v[u][k];
             if constexpr (T::mean) {
-                p.v[u][k] = gv;
+                // A value of its own, or its copy stands right behind the
+                // sample's load and waits for it (balanced tree of 6, d =
+                // 10,000,001 473 | 407 us per round with this line).
+                float q = gv;
+                asm("" : "+v"(q));
+                p.v[u][k] = q;
             } else if constexpr (T::grad) {
                 const float st = a.lr * gv;
                 p.v[u][k] = -st;
@@ -2902,25 +2927,26 @@ enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kP
 // partial 64-byte blocks dearest, so rows with d % 16 != 0 gain most from
 // long runs, and rows of whole 128-byte lines (d % 32 == 0) little or less
 // than nothing.  us per round on MI355X, runs of 1 | 2 | 8 | 16 tiles, timed in
-// turn on the same arrays (medians of 15, which repeat within 0.5%; Adam 1%):
-//   tile kernel   chain of 16, d = 9.75M         925 |  920 |  918 |
-//                 the same, no momentum          703 |  696 |  699 |
-//                 d = 9,750,016 (whole lines)    897 |  910 |  907 |
-//                 d = 9,750,001                  983 |  972 |  970 |  974
-//                 random 24, d = 2,000,003       322 |  317 |  318 |  318
-//                 Adam, d = 9,750,001           1270 | 1310 | 1244 | 1246
-//                 Adam, d = 9.75M               1192 | 1211 | 1176 |
-//   cluster       chain of 64, d = 9.75M        4133 | 4149 | 4116 | 4071
-//                 2,000 with hubs, d = 150,000  2209 | 2185 | 2128 | 2108
-//                 random 1,000, d = 200,001     1503 | 1473 | 1424 | 1419
-//                 random 256, d = 1,000,016     1716 | 1709 | 1687 | 1701
-//                 random 256, d = 1M (lines)    1690 | 1698 | 1679 | 1694
+// turn on the same arrays (medians of 13, which repeat within 1%; Adam and
+// streaming rows of odd length 2%):
+//   tile kernel   chain of 16, d = 9.75M         932 |  909 |  919 |
+//                 the same, no momentum          711 |  701 |  707 |
+//                 d = 9,750,016 (whole lines)    907 |  904 |  914 |
+//                 d = 9,750,001                  990 | 1000 |  978 |  970
+//                 random 24, d = 2,000,003       326 |  320 |  320 |  320
+//                 Adam, d = 9,750,001           1291 | 1319 | 1261 | 1255
+//                 Adam, d = 9.75M               1220 | 1201 | 1208 |
+//   cluster       chain of 64, d = 9.75M        4161 | 4174 | 4159 | 4086
+//                 2,000 with hubs, d = 150,000  2203 | 2180 | 2118 | 2118
+//                 random 1,000, d = 200,001     1520 | 1487 | 1432 | 1421
+//                 random 256, d = 1,000,016     1738 | 1733 | 1707 | 1718
+//                 random 256, d = 1M (lines)    1712 | 1716 | 1717 | 1718
 //   double trees, one after the other
-//                 64, d = 9.75M                 4046 | 4472 | 3998 | 3950
-//                 40, d = 4,000,001             1055 |      | 1051 | 1028
-//                 40, d = 4M (lines)             974 |      | 1006 |  981
-//   in clusters   200, d = 1,000,016            1316 | 1308 | 1309 | 1303
-//                 100, d = 100,001              90.7 |      | 89.0 | 89.3
+//                 64, d = 9.75M                 4071 | 4382 | 4066 | 4000
+//                 40, d = 4,000,001             1071 | 1072 | 1058 | 1044
+//                 40, d = 4M (lines)             981 |  996 | 1002 |  986
+//   in clusters   200, d = 1,000,016            1367 | 1342 | 1354 | 1329
+//                 100, d = 100,001              90.8 | 90.9 | 89.8 | 89.1
 // Runs of 32 and 64 tiles were no faster.  The double-tree kernel with both
 // trees in LDS was slower with every run (16 workers, d = 9.75M, ms: .889 |
 // .925 | .898 | .899) and owns its tiles in launch order.  The rule looks at d
@@ -2943,20 +2969,20 @@ static int tile_run_shift(bool adam, int64_t d, bool nt) {
 // of a few workgroups per CU (one at a time fits) ends with a whole dispatch
 // round of the large ones where launch order fills the slots that the small
 // ones leave.  Below 3 workgroups per CU, us per round, runs of 1 | 8 | 16:
-//   single trees  chain of 40, d = 45,557        20.6 | 19.8 | 20.9
-//                 100 with hubs, d = 38,389      47.1 | 48.1 | 50.9
-//                 random 300, d = 17,003         50.0 | 48.7 | 50.2
-//                 random 1,000, d = 7,001        67.2 | 64.8 | 66.9
-//                 chain of 64, d = 67,061        39.1 | 36.8 | 37.5
-//   double trees  70 (3 clusters), d = 50,001    38.5 | 38.6 | 44.8
-//                 130 (5), d = 27,637            39.1 | 46.0 | 45.9
-//                 200 (7), d = 20,001            42.1 | 47.9 | 47.3
-//                 100 (4), d = 67,061            68.3 | 66.7 | 66.8
-//                 256 (8), d = 18,421            50.5 | 50.1 | 49.6
+//   single trees  chain of 40, d = 45,557        20.7 | 20.5 | 21.2
+//                 100 with hubs, d = 38,389      46.6 | 47.7 | 50.1
+//                 random 300, d = 17,003         50.6 | 49.0 | 50.6
+//                 random 1,000, d = 7,001        67.3 | 65.6 | 67.3
+//                 chain of 64, d = 67,061        39.8 | 38.4 | 38.3
+//   double trees  70 (3 clusters), d = 50,001    38.9 | 38.9 | 45.3
+//                 130 (5), d = 27,637            39.5 | 46.6 | 46.9
+//                 200 (7), d = 20,001            42.4 | 48.2 | 47.8
+//                 100 (4), d = 67,061            69.2 | 67.6 | 67.4
+//                 256 (8), d = 18,421            49.7 | 50.4 | 49.6
 // With 4, 8, .. clusters launch order leaves an XCD to one or two of them
 // anyway, so double trees keep their runs there.  From 3 workgroups per CU on
 // runs of 16 are the best or within 1% of it but for a last round of 70
-// workers (d = 176,629, 4.04 workgroups per CU: 98.7 | 98.8 | 102.3).
+// workers (d = 176,629, 4.04 workgroups per CU: 98.6 | 99.2 | 102.2).
 static int cluster_run_shift(Path path, int64_t d, int64_t workgroups, int count, int cu_count) {
     if (d % 32 == 0) return 0;
     if (path == kPathDTreeSeq || workgroups >= 3 * (int64_t)cu_count) return 4;
@@ -3078,20 +3104,20 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             // blocks of 256 threads per CU, and 8 with hubs, whose threads
             // each walk a hub's messages.  us per round on MI355X, timed in
             // turn, one float | chunks, at blocks of chunks per CU:
-            //   chain of 64, d = 288,000            6.6   127.4 | 125.7
-            //   chain of 256, d = 64,000            7.4   121.3 | 119.1
-            //   balanced tree of 100, d = 192,000   6.6   131.2 | 129.0
-            //   random 1,000, d = 10,240            5.2    85.0 |  84.1
-            //   random 100, d = 100,001             5.4    89.0 |  88.8
-            //   random 300, d = 32,001              4.4    81.1 |  81.7
-            //   random 100, d = 64,000              3.5    55.6 |  56.7
-            //   balanced tree of 100, d = 64,000    2.2    48.1 |  49.3
-            //   hubs 300, d = 160,768               8.0   343.2 | 341.7
-            //   hubs 600, d = 76,801                7.6   355.1 | 357.8
-            //   hubs 100, d = 240,001               5.5   181.8 | 184.6
-            //   hubs 2,000, d = 6,400               2.1   143.7 | 150.3
+            //   chain of 64, d = 288,000            6.6   127.0 | 125.5
+            //   chain of 256, d = 64,000            7.4   120.7 | 118.2
+            //   balanced tree of 100, d = 192,000   6.6   130.6 | 128.8
+            //   random 1,000, d = 10,240            5.2    84.3 |  84.4
+            //   random 100, d = 100,001             5.4    88.8 |  88.7
+            //   random 300, d = 32,001              4.4    81.5 |  81.9
+            //   random 100, d = 64,000              3.5    55.4 |  57.0
+            //   balanced tree of 100, d = 64,000    2.2    48.2 |  49.0
+            //   hubs 300, d = 160,768               8.0   339.9 | 337.8
+            //   hubs 600, d = 76,801                7.6   351.2 | 354.6
+            //   hubs 100, d = 240,001               5.5   181.2 | 184.1
+            //   hubs 2,000, d = 6,400               2.1   143.5 | 149.3
             // (2,000 workers with hubs gain from single floats up to 16:
-            // d = 53,225 816 | 824.)
+            // d = 53,225 802 | 809.)
             L.wide = (h->d / 4 + 255) / 256 * (int64_t)h->cl_nb >=
                      (h->cl_hubs ? 8 : 5) * (int64_t)h->cu_count;
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,
