@@ -281,23 +281,26 @@ __device__ __forceinline__ void store_float(float *p, float v) {
 // when d % C != 0.  Whole chunks move as one access, the tail float by float.
 // Without TAIL the code is that of the bool-mask form.
 //
-// With TAIL a chunk stays one vector up to its last assignment, and the tail
-// is a second step rather than the other branch.  Merged float by float, some
-// of a chunk's floats ended in registers of their own, copied right behind
-// the load, and each copy waits for every load in flight: up to four of a
-// worker's rows came one after the other.  us per round on MI355X, before |
-// after: chain of 3, SGD, d = 20,000,001 339 | 284; balanced tree of 8, Adam,
-// d = 3,000,001 206 | 189; chain of 16, d = 1,250,001 128 | 125; double trees
-// of 2, SGD, d = 20,000,001 144 | 115.  In the caches a few rounds lose (double
-// trees of 12, d = 166,667 14.4 | 15.2), most gain (balanced tree of 8, d =
-// 12,501 7.1 | 6.4).
-template <int U, int C, bool NT, bool TAIL>
+// With TAIL and APART a chunk stays one vector up to its last assignment, and
+// the tail is a second step rather than the other branch.  Merged float by
+// float, some of a chunk's floats end in registers of their own, copied right
+// behind the load, and each copy waits for every load in flight: up to four of
+// a worker's rows came one after the other in the tile kernel.  us per round
+// on MI355X, merged | apart: chain of 3, SGD, d = 20,000,001 339 | 284;
+// balanced tree of 8, Adam, d = 3,000,001 206 | 189; chain of 16, d = 1,250,001
+// 128 | 125; double trees of 2, SGD, d = 20,000,001 144 | 115.  In the caches a
+// few rounds lose (double trees of 12, d = 166,667 14.4 | 15.2), most gain
+// (balanced tree of 8, d = 12,501 7.1 | 6.4).  The other kernels, a worker or
+// more to each of 16 waves, hide those waits and merge: apart, 0 to 2% less on
+// average but 3 to 5% more on some (57 with hubs, SGD, d = 441,079 153 | 160; 38
+// on double trees, d = 26,239 18.4 | 19.1).
+template <int U, int C, bool NT, bool TAIL, bool APART = false>
 __device__ __forceinline__ lanev<U, C> load_lane(const float *row, int lane, const int (&nv)[U]) {
     lanev<U, C> r;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const float *p = row + (u * 64 + lane) * C;
-        if constexpr (TAIL && C == 4) {
+        if constexpr (TAIL && APART && C == 4) {
             f4_t t = {0.0f, 0.0f, 0.0f, 0.0f};
             if (nv[u] == C) {
                 const f4u_t *q = reinterpret_cast<const f4u_t *>(p);
@@ -311,9 +314,12 @@ __device__ __forceinline__ lanev<U, C> load_lane(const float *row, int lane, con
             r.v[u][0] = t.x; r.v[u][1] = t.y; r.v[u][2] = t.z; r.v[u][3] = t.w;
         } else if (nv[u] == C) {
             load_chunk<C, NT>(p, r.v[u]);
+        } else if constexpr (TAIL) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) r.v[u][k] = k < nv[u] ? load_float<NT>(p + k) : 0.0f;
         } else {
 #pragma unroll
-            for (int k = 0; k < C; ++k) r.v[u][k] = TAIL && k < nv[u] ? load_float<NT>(p + k) : 0.0f;
+            for (int k = 0; k < C; ++k) r.v[u][k] = 0.0f;
         }
     }
     return r;
@@ -852,10 +858,10 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
         if (i >= a.n) break;
         const int64_t row = (int64_t)i * a.d + base;
         lanev<U, C> xv = zero_lane<U, C>(), s1 = zero_lane<U, C>(), s2 = zero_lane<U, C>();
-        if constexpr (T::reads_x) xv = load_lane<U, C, NT, TAIL>(a.x + row, lane, ok);
-        const lanev<U, C> gv = load_lane<U, C, NT, TAIL>(a.g + row, lane, ok);
-        if constexpr (T::uses_s1) s1 = load_lane<U, C, NT, TAIL>(a.s1 + row, lane, ok);
-        if constexpr (T::uses_s2) s2 = load_lane<U, C, NT, TAIL>(a.s2 + row, lane, ok);
+        if constexpr (T::reads_x) xv = load_lane<U, C, NT, TAIL, true>(a.x + row, lane, ok);
+        const lanev<U, C> gv = load_lane<U, C, NT, TAIL, true>(a.g + row, lane, ok);
+        if constexpr (T::uses_s1) s1 = load_lane<U, C, NT, TAIL, true>(a.s1 + row, lane, ok);
+        if constexpr (T::uses_s2) s2 = load_lane<U, C, NT, TAIL, true>(a.s2 + row, lane, ok);
         const int s0 = uniform(a.row_ptr[i]);
         const int deg = uniform(a.row_ptr[i + 1]) - s0;
         lanev<U, C> o[kMaxDegInRegs];
@@ -864,7 +870,7 @@ __global__ void __launch_bounds__(1024) relaysum_tile_kernel(RoundArgs a) {
             for (int b = 0; b < kMaxDegInRegs; ++b) {
                 if (b < relayed(deg)) {
                     const int in_slot = uniform(a.rev[s0 + b]);
-                    o[b] = load_lane<U, C, NT, TAIL>(a.ring_prev + ring_off(a, in_slot, base), lane, ok);
+                    o[b] = load_lane<U, C, NT, TAIL, true>(a.ring_prev + ring_off(a, in_slot, base), lane, ok);
                 }
             }
         }
@@ -1249,8 +1255,9 @@ __device__ __forceinline__ void emit_pair_messages(const RoundArgs &a, float *s_
 //
 // A short round whose rows and ring stay in the MALL runs with
 // cache-allocating accesses (NT = false, as in the tile kernel): on MI355X 24
-// workers at d = 150,001 30.6 -> 26.7 us per round, 16 with Adam at d = 250,000
-// 34.5 -> 30.6 us, 16 at d = 270,000 (of the range's end) 31.6 -> 31.3 us.
+// workers at d = 150,001 30.4 -> 26.3 us per round, 16 with Adam at d = 250,000
+// 35.0 -> 30.6 us, 16 at d = 270,000 (of the range's end) 30.7 -> 30.5 us (in
+// part from the leaves' messages that are no longer read).
 template <int PW, int R, bool NT, bool TAIL>
 __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, RoundArgs b) {
     using T = RuleOf<R>;
@@ -1296,10 +1303,10 @@ __global__ void __launch_bounds__(1024) relaysum_dtree_kernel(RoundArgs a, Round
         if (i >= a.n) break;
         const int64_t row = (int64_t)i * a.d + base;
         lanev<U, 4> xv = zero_lane<U, 4>(), s1 = zero_lane<U, 4>(), s2 = zero_lane<U, 4>();
-        if constexpr (T::reads_x) xv = load_lane<U, 4, NT, TAIL>(a.x + row, lane, ok);
-        const lanev<U, 4> gv = load_lane<U, 4, NT, TAIL>(a.g + row, lane, ok);
-        if constexpr (T::uses_s1) s1 = load_lane<U, 4, NT, TAIL>(a.s1 + row, lane, ok);
-        if constexpr (T::uses_s2) s2 = load_lane<U, 4, NT, TAIL>(a.s2 + row, lane, ok);
+        if constexpr (T::reads_x) xv = load_lane<U, 4, NT, TAIL, true>(a.x + row, lane, ok);
+        const lanev<U, 4> gv = load_lane<U, 4, NT, TAIL, true>(a.g + row, lane, ok);
+        if constexpr (T::uses_s1) s1 = load_lane<U, 4, NT, TAIL, true>(a.s1 + row, lane, ok);
+        if constexpr (T::uses_s2) s2 = load_lane<U, 4, NT, TAIL, true>(a.s2 + row, lane, ok);
         const int s0a = ldc(a.row_ptr + i), dega = ldc(a.row_ptr + i + 1) - s0a;
         const int s0b = ldc(b.row_ptr + i), degb = ldc(b.row_ptr + i + 1) - s0b;
         pair2_t oa[kMaxDegInRegs], ob[kMaxDegInRegs];
@@ -2939,24 +2946,24 @@ enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kP
 // than nothing.  us per round on MI355X, runs of 1 | 2 | 8 | 16 tiles, timed in
 // turn on the same arrays (medians of 13, which repeat within 1%; Adam and
 // streaming rows of odd length 2%):
-//   tile kernel   chain of 16, d = 9.75M         932 |  909 |  919 |
-//                 the same, no momentum          711 |  701 |  707 |
-//                 d = 9,750,016 (whole lines)    907 |  904 |  914 |
-//                 d = 9,750,001                  990 | 1000 |  978 |  970
-//                 random 24, d = 2,000,003       326 |  320 |  320 |  320
-//                 Adam, d = 9,750,001           1291 | 1319 | 1261 | 1255
-//                 Adam, d = 9.75M               1220 | 1201 | 1208 |
-//   cluster       chain of 64, d = 9.75M        4161 | 4174 | 4159 | 4086
-//                 2,000 with hubs, d = 150,000  2203 | 2180 | 2118 | 2118
-//                 random 1,000, d = 200,001     1520 | 1487 | 1432 | 1421
-//                 random 256, d = 1,000,016     1738 | 1733 | 1707 | 1718
-//                 random 256, d = 1M (lines)    1712 | 1716 | 1717 | 1718
+//   tile kernel   chain of 16, d = 9.75M         929 |  904 |  917 |
+//                 the same, no momentum          708 |  699 |  704 |
+//                 d = 9,750,016 (whole lines)    902 |  898 |  911 |
+//                 d = 9,750,001                  981 | 1000 |  967 |  965
+//                 random 24, d = 2,000,003       325 |  320 |  320 |  319
+//                 Adam, d = 9,750,001           1290 | 1317 | 1273 | 1257
+//                 Adam, d = 9.75M               1229 | 1208 | 1195 |
+//   cluster       chain of 64, d = 9.75M        4114 | 4122 | 4095 | 4050
+//                 2,000 with hubs, d = 150,000  2196 | 2169 | 2118 | 2109
+//                 random 1,000, d = 200,001     1513 | 1487 | 1444 | 1428
+//                 random 256, d = 1,000,016     1734 | 1739 | 1714 | 1722
+//                 random 256, d = 1M (lines)    1702 | 1714 | 1697 | 1713
 //   double trees, one after the other
-//                 64, d = 9.75M                 4071 | 4382 | 4066 | 4000
-//                 40, d = 4,000,001             1071 | 1072 | 1058 | 1044
-//                 40, d = 4M (lines)             981 |  996 | 1002 |  986
-//   in clusters   200, d = 1,000,016            1367 | 1342 | 1354 | 1329
-//                 100, d = 100,001              90.8 | 90.9 | 89.8 | 89.1
+//                 64, d = 9.75M                 4036 | 4330 | 4032 | 3983
+//                 40, d = 4,000,001             1072 | 1078 | 1060 | 1049
+//                 40, d = 4M (lines)             981 |  994 |  999 |  985
+//   in clusters   200, d = 1,000,016            1363 | 1339 | 1339 | 1325
+//                 100, d = 100,001              90.2 | 90.6 | 89.2 | 88.5
 // Runs of 32 and 64 tiles were no faster.  The double-tree kernel with both
 // trees in LDS was slower with every run (16 workers, d = 9.75M, ms: .889 |
 // .925 | .898 | .899) and owns its tiles in launch order.  The rule looks at d
@@ -2969,7 +2976,7 @@ enum Path { kPathTile, kPathDTree, kPathCluster, kPathTwoPass, kPathDTreeSeq, kP
 // shared lines there, equal to 1% with runs; their variants have no mapping.
 static int tile_run_shift(bool adam, int64_t d, bool nt) {
     if (!nt) return 0;
-    return d % 16 != 0 ? 3 : adam ? 0 : 1;
+    return d % 16 != 0 ? 4 : adam ? 0 : 1;
 }
 
 // The cluster kernels and the sequential double-tree kernel, in the caches
@@ -2979,20 +2986,20 @@ static int tile_run_shift(bool adam, int64_t d, bool nt) {
 // of a few workgroups per CU (one at a time fits) ends with a whole dispatch
 // round of the large ones where launch order fills the slots that the small
 // ones leave.  Below 3 workgroups per CU, us per round, runs of 1 | 8 | 16:
-//   single trees  chain of 40, d = 45,557        20.7 | 20.5 | 21.2
-//                 100 with hubs, d = 38,389      46.6 | 47.7 | 50.1
-//                 random 300, d = 17,003         50.6 | 49.0 | 50.6
-//                 random 1,000, d = 7,001        67.3 | 65.6 | 67.3
-//                 chain of 64, d = 67,061        39.8 | 38.4 | 38.3
-//   double trees  70 (3 clusters), d = 50,001    38.9 | 38.9 | 45.3
-//                 130 (5), d = 27,637            39.5 | 46.6 | 46.9
-//                 200 (7), d = 20,001            42.4 | 48.2 | 47.8
-//                 100 (4), d = 67,061            69.2 | 67.6 | 67.4
-//                 256 (8), d = 18,421            49.7 | 50.4 | 49.6
+//   single trees  chain of 40, d = 45,557        20.8 | 20.3 | 21.2
+//                 100 with hubs, d = 38,389      47.4 | 48.4 | 50.3
+//                 random 300, d = 17,003         50.1 | 48.6 | 49.9
+//                 random 1,000, d = 7,001        67.3 | 65.2 | 66.7
+//                 chain of 64, d = 67,061        39.5 | 38.7 | 38.9
+//   double trees  70 (3 clusters), d = 50,001    38.4 | 38.3 | 44.8
+//                 130 (5), d = 27,637            38.9 | 46.2 | 46.6
+//                 200 (7), d = 20,001            42.0 | 47.4 | 47.4
+//                 100 (4), d = 67,061            68.5 | 67.3 | 67.0
+//                 256 (8), d = 18,421            49.8 | 50.0 | 49.7
 // With 4, 8, .. clusters launch order leaves an XCD to one or two of them
 // anyway, so double trees keep their runs there.  From 3 workgroups per CU on
 // runs of 16 are the best or within 1% of it but for a last round of 70
-// workers (d = 176,629, 4.04 workgroups per CU: 98.6 | 99.2 | 102.2).
+// workers (d = 176,629, 4.04 workgroups per CU: 98.0 | 98.7 | 101.6).
 static int cluster_run_shift(Path path, int64_t d, int64_t workgroups, int count, int cu_count) {
     if (d % 32 == 0) return 0;
     if (path == kPathDTreeSeq || workgroups >= 3 * (int64_t)cu_count) return 4;
@@ -3114,20 +3121,20 @@ static int resolve_launch(relaysum_t *h, int rule, bool c4) {
             // blocks of 256 threads per CU, and 8 with hubs, whose threads
             // each walk a hub's messages.  us per round on MI355X, timed in
             // turn, one float | chunks, at blocks of chunks per CU:
-            //   chain of 64, d = 288,000            6.6   127.0 | 125.5
-            //   chain of 256, d = 64,000            7.4   120.7 | 118.2
-            //   balanced tree of 100, d = 192,000   6.6   130.6 | 128.8
-            //   random 1,000, d = 10,240            5.2    84.3 |  84.4
-            //   random 100, d = 100,001             5.4    88.8 |  88.7
-            //   random 300, d = 32,001              4.4    81.5 |  81.9
-            //   random 100, d = 64,000              3.5    55.4 |  57.0
-            //   balanced tree of 100, d = 64,000    2.2    48.2 |  49.0
-            //   hubs 300, d = 160,768               8.0   339.9 | 337.8
-            //   hubs 600, d = 76,801                7.6   351.2 | 354.6
-            //   hubs 100, d = 240,001               5.5   181.2 | 184.1
-            //   hubs 2,000, d = 6,400               2.1   143.5 | 149.3
+            //   chain of 64, d = 288,000            6.6   127.0 | 125.3
+            //   chain of 256, d = 64,000            7.4   120.6 | 118.2
+            //   balanced tree of 100, d = 192,000   6.6   130.3 | 128.2
+            //   random 1,000, d = 10,240            5.2    83.5 |  83.5
+            //   random 100, d = 100,001             5.4    89.8 |  89.1
+            //   random 300, d = 32,001              4.4    80.6 |  80.7
+            //   random 100, d = 64,000              3.5    55.8 |  56.9
+            //   balanced tree of 100, d = 64,000    2.2    48.2 |  49.1
+            //   hubs 300, d = 160,768               8.0   337.6 | 337.1
+            //   hubs 600, d = 76,801                7.6   351.3 | 354.5
+            //   hubs 100, d = 240,001               5.5   181.0 | 183.3
+            //   hubs 2,000, d = 6,400               2.1   143.6 | 149.3
             // (2,000 workers with hubs gain from single floats up to 16:
-            // d = 53,225 802 | 809.)
+            // d = 53,225 807 | 813.)
             L.wide = (h->d / 4 + 255) / 256 * (int64_t)h->cl_nb >=
                      (h->cl_hubs ? 8 : 5) * (int64_t)h->cu_count;
             if (!pick_cluster(rule, h->cl_relay, h->cl_cap / kMaxWaves, nt, h->d % 4 != 0,

@@ -21,19 +21,19 @@ pytestmark = pytest.mark.gpu
 T = 512   # coordinates of a tile
 
 # path, tree, n, d.  Tile kernel: past half of the MALL (432*d bytes at 16
-# workers), runs of 8 for d % 16 != 0 and pairs otherwise.  The cluster
+# workers), runs of 16 for d % 16 != 0 and pairs otherwise.  The cluster
 # kernels and dtree_seq for d % 32 != 0: runs of 16, but below 3 workgroups per
 # CU runs of 8 on single trees and launch order on double trees whose number of
 # clusters is no multiple of 4; by 1 otherwise.  dtree: launch order, here on
 # both sides of the cache-allocating accesses.
 CASES = [
-    ("tile", "chain", 16, 640 * T - 1),        # ten cycles of 64 tiles exactly
+    ("tile", "chain", 16, 640 * T - 1),        # five cycles of 128 tiles exactly
     ("tile", "chain", 16, 640 * T + 1),        # one tile past them
     ("tile", "heap", 16, 671 * T + 16),        # pairs, 42 cycles of 16
     ("tile", "chain", 20, 639 * T + 5),        # two workers in some waves, inside a cycle
     # 124 KB of messages, one workgroup per CU: 512 workgroups in two dispatch
     # rounds of 256, the excess over 512 tiles as spill coordinates, whose
-    # owners are in launch order beside tiles in runs of 8 and in pairs.
+    # owners are in launch order beside tiles in runs of 16 and in pairs.
     ("tile", "chain", 32, 270_001),
     ("tile", "chain", 32, 270_000),
     ("cluster", "chain", 40, 36 * T + 3),      # runs of 8, inside a cycle of 8 * 8
